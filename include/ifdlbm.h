@@ -114,7 +114,8 @@ typedef struct {
     int32_t batched;        /* 1: all cavities in one launch per step; 0: one launch per cavity       */
     int32_t graph_steps;    /* > 0: replay steps from a captured HIP graph of this many steps         */
     int32_t dt_rule;        /* IFDLBM_DT_CONTRAVARIANT | IFDLBM_DT_CARTESIAN                          */
-    int32_t segment_rows;   /* fused kernel: rows per work item, 0 = automatic, else in [8, 4096]     */
+    int32_t segment_rows;   /* fused kernel: rows per work item of its row march, in [8, 4096]; 0 = automatic:
+                               also takes small batches to tiles of one node per thread (same results) */
     int32_t lambda_mode;    /* IFDLBM_LAMBDA_LAGGED (the paper's, default) | IFDLBM_LAMBDA_IMPLICIT    */
     int32_t pressure_residual; /* IFDLBM_EP_MEAN_REMOVED (default) | IFDLBM_EP_PRINTED                  */
     void*   hip_stream;     /* hipStream_t to enqueue on, or NULL: the handle creates its own         */
@@ -221,10 +222,10 @@ int ifdlbm_set_state(ifdlbm_t* h, int32_t cav, const double* fhat, const double*
 int ifdlbm_status(ifdlbm_t* h, int32_t cav);
 
 /* Tile-shape autotuner of the fused kernel: times steps_per_trial steps (after one warm-up step) of the
-   handle's running cavities for every candidate row-segment length (16 ... 128 rows), keeps the fastest in
-   options.segment_rows, and restores the state, step count, residual sums and random-word counter, so later results are those
+   handle's running cavities for every candidate row-segment length (8 ... 128 rows) and, where the automatic choice is
+   a tile, for that tile, keeps the fastest, and restores the state, step count, residual sums and random-word counter, so later results are those
    without the call (they do not depend on the segmentation).  *segment_rows and *ms_per_step (either may be
-   NULL) receive the choice and its time per step; 0 for the staged schedule, which has no tile shape.  Device
+   NULL) receive the choice (rows per segment or of the tile) and its time per step; 0 for the staged schedule, which has no tile shape.  Device
    memory for one copy of the state is allocated and freed inside the call, which synchronises the stream.
    Errors: EINVAL (steps_per_trial outside [1, 10000]), ENOMEM, EDEVICE. */
 int ifdlbm_autotune(ifdlbm_t* h, int32_t steps_per_trial, int32_t* segment_rows, double* ms_per_step);

@@ -63,7 +63,6 @@ constexpr double kCs2 = 1.0 / 3.0;
 // recomputed halo rows) that still gives kTargetItems work items, so that the
 // GPU stays full through the tail of a launch; the shortest otherwise.
 constexpr int kSegCandidates[] = {128, 96, 80, 72, 64, 56, 48, 40, 32, 24, 16, 8};
-constexpr int kMinSegRows = 8;
 constexpr int kTargetItems = 4096;
 constexpr int kXcds = 8;   // MI355X: workgroups are dealt to the 8 XCDs in turn
 
@@ -109,7 +108,8 @@ struct ifdlbm_s {
     StripItem* d_act_items = nullptr;
     std::vector<StripItem> act_sorted;     // the same items, longest first (batched launch)
     StripItem* d_act_sorted = nullptr;
-    size_t max_units = 0;
+    std::vector<int> cav_shape;            // kernel of each cavity's items: a tile shape, or kMarch
+    size_t units_alloc = 0, items_alloc = 0, sorted_alloc = 0;   // entries of d_partial and of the item lists
     std::vector<int32_t> unit_first, unit_count;   // per cavity, in the active unit list
     int32_t *d_unit_first = nullptr, *d_unit_count = nullptr;
     double* d_partial = nullptr;
@@ -137,6 +137,31 @@ struct ifdlbm_s {
 
 namespace {
 
+template <typename P>
+int dalloc(P** p, size_t bytes)
+{
+    hipError_t e = hipMalloc(reinterpret_cast<void**>(p), std::max<size_t>(bytes, 256));
+    if (e != hipSuccess) {
+        *p = nullptr;
+        return fail(e == hipErrorOutOfMemory ? IFDLBM_ENOMEM : IFDLBM_EDEVICE,
+                    std::string("hipMalloc(") + std::to_string(bytes) + "): " + hipGetErrorString(e));
+    }
+    return IFDLBM_OK;
+}
+
+// Device array of at least n entries (n_alloc: the entries it has); its contents are not kept.
+template <typename P>
+int grow(P** p, size_t& n_alloc, size_t n, size_t entry)
+{
+    if (n <= n_alloc) return IFDLBM_OK;
+    if (*p) IFD_HIP(hipFree(*p));
+    *p = nullptr;
+    n_alloc = 0;
+    const int rc = dalloc(p, n * entry);
+    if (!rc) n_alloc = n;
+    return rc;
+}
+
 int units_per_step(const ifdlbm_s* h) { return h->opt.kernel == IFDLBM_KERNEL_STAGED ? 5 : 1; }
 
 // Rebuild the unit lists of the running cavities (after creation, retirement or restore).
@@ -154,6 +179,47 @@ int segment_start(int g, int ng, int ny)
     const int b = (int)((int64_t)g * ny / ng);
     const int r = ((b - 4) % 5 + 5) % 5;
     return r <= 2 ? b - r : b + (5 - r);
+}
+
+// Kernel of the fused schedule for one launch (all running cavities, or cavity one_cav alone): a tile shape of
+// step_tile.hip, or kMarch, the row march of step_fused.hip.  A march item is a chain of at least 16 rows (35 us in
+// FP32, 43 us in FP64, however small the cavity), a tile a chain of one node per stage; but tiles recompute more halo,
+// so the march wins once its items fill the GPU.  Microseconds per step, march against tile shapes 0, 1, 2 (side x
+// cavities; FP32SRF, then FP64):
+//   33 x 1     35.0 /  5.2   5.7   7.9     43.4 /  5.7   7.4   9.5
+//   65 x 4     35.5 /  5.9   6.0   8.9     43.3 /  7.5   7.9  11.1
+//   65 x 8     35.2 /  7.2   6.4   9.0     43.5 / 10.9   8.7  11.3
+//   193 x 2    35.6 / 10.3   8.3   9.6     44.2 / 15.8  11.8  12.1
+//   129 x 6    36.5 / 12.4  11.3   9.8     44.9 / 19.5  15.2  12.6
+//   193 x 4    37.2 / 15.7  13.4  12.5     45.0 / 25.5  18.0  20.6
+//   513 x 2    37.8 / 37.7  29.2  25.7     62.9 / 72.5  40.8  43.5
+//   513 x 4    54.9 / 67.2  52.6  37.5     96.4 /  132  71.0  68.8
+//   513 x 12    120 /  191   150  94.8      255 /  465   248   227
+//   513 x 16    149 /  307   230   146      289 /  618   330   299
+// Shapes 0 and 1 stay ahead while they have at most two workgroups per CU.  In FP64 shape 2 has room for one workgroup
+// per CU only: a second round of it loses to shape 1 until there are about six.
+constexpr int kMarch = -1;
+
+int choose_kernel(const ifdlbm_s* h, int one_cav = -1)
+{
+    if (h->opt.segment_rows > 0) return kMarch;   // rows per item asked for: the march's
+    int64_t nodes = 0, tiles[kTileShapes] = {};
+    for (int c = 0; c < h->n_cav; ++c) {
+        const CavityDesc& d = h->desc[c];
+        if (!d.active || (one_cav >= 0 && c != one_cav)) continue;
+        nodes += (int64_t)d.nx * d.ny;
+        for (int s = 0; s < kTileShapes; ++s) tiles[s] += (int64_t)ceil_div(d.nx, kTileCols[s]) * ceil_div(d.ny, kTileRows[s]);
+    }
+    constexpr int64_t kCus = 256;
+    if (tiles[0] <= 2 * kCus) return 0;
+    if (tiles[1] <= 2 * kCus) return 1;
+    const int prec = h->opt.precision;
+    const bool wide = t_elem_size(prec) == 8;
+    // nodes up to which shape 2 is ahead of the march (513 x 512 cavities: FP64 13, FP32SRF 16, FP32 11, FP16DEV 24 and
+    // more: its 44 bytes per node leave it bound by instructions, which four wavefronts per SIMD issue faster)
+    const int64_t most = wide ? 3500000 : prec == P_FP32SRF ? 4000000 : prec == P_FP32 ? 3000000 : 8000000;
+    if (nodes > most) return kMarch;
+    return wide && tiles[2] > kCus && tiles[2] < 6 * kCus ? 1 : 2;
 }
 
 // Rows per segment for the cavities of one launch: all running cavities (one_cav < 0, batched launch) or
@@ -216,11 +282,14 @@ int rebuild_worklists(ifdlbm_s* h)
 {
     h->act_blocks.clear();
     h->act_items.clear();
-    const int seg_batch = segment_rows(h);
+    const int seg_batch = segment_rows(h), shape_batch = choose_kernel(h);
+    h->cav_shape.assign(h->n_cav, kMarch);
     for (int c = 0; c < h->n_cav; ++c) {
         const bool run = h->desc[c].active != 0;
-        // a launch of its own fills the GPU only with the cavity's own segment length
+        // a launch of its own fills the GPU only with the cavity's own segment length or tile
         const int seg = h->opt.batched ? seg_batch : segment_rows(h, c);
+        const int shape = h->opt.batched ? shape_batch : choose_kernel(h, c);
+        h->cav_shape[c] = shape;
         if (h->opt.kernel == IFDLBM_KERNEL_STAGED) {
             h->unit_first[c] = (int32_t)h->act_blocks.size();
             if (run) {
@@ -232,17 +301,28 @@ int rebuild_worklists(ifdlbm_s* h)
             h->unit_first[c] = (int32_t)h->act_items.size();
             if (run) {
                 const CavityDesc& d = h->desc[c];
-                const int ns = ceil_div(d.nx, kStripOut), ng = ceil_div(d.ny, seg);
+                const bool march = shape == kMarch;
+                const int ns = ceil_div(d.nx, march ? kStripOut : kTileCols[shape]);
+                const int ng = ceil_div(d.ny, march ? seg : kTileRows[shape]);
+                auto row = [&](int g) { return march ? segment_start(g, ng, d.ny) : (int)((int64_t)g * d.ny / ng); };
                 for (int g = 0; g < ng; ++g)
                     for (int s = 0; s < ns; ++s)
-                        h->act_items.push_back({c, (int16_t)(s * d.nx / ns), (int16_t)((s + 1) * d.nx / ns),
-                                                segment_start(g, ng, d.ny), segment_start(g + 1, ng, d.ny),
-                                                (int32_t)h->act_items.size()});
+                        h->act_items.push_back({c, (int16_t)(s * d.nx / ns), (int16_t)((s + 1) * d.nx / ns), row(g),
+                                                row(g + 1), (int32_t)h->act_items.size()});
             }
             h->unit_count[c] = (int32_t)h->act_items.size() - h->unit_first[c];
         }
     }
     order_for_batch(h);
+    // the lists grow with the item count of the chosen kernel; nothing of the old ones is kept
+    int rc = IFDLBM_OK;
+    const size_t units = h->opt.kernel == IFDLBM_KERNEL_STAGED ? h->act_blocks.size() : h->act_items.size();
+    if (units > h->units_alloc || h->act_items.size() > h->items_alloc || h->act_sorted.size() > h->sorted_alloc)
+        IFD_HIP(hipStreamSynchronize(h->stream));
+    rc = grow(&h->d_partial, h->units_alloc, units, kPartials * sizeof(double));
+    if (!rc) rc = grow(&h->d_act_items, h->items_alloc, h->act_items.size(), sizeof(StripItem));
+    if (!rc) rc = grow(&h->d_act_sorted, h->sorted_alloc, h->act_sorted.size(), sizeof(StripItem));
+    if (rc) return rc;
     if (!h->act_blocks.empty())
         IFD_HIP(hipMemcpyAsync(h->d_act_blocks, h->act_blocks.data(), h->act_blocks.size() * sizeof(NodeBlock),
                                hipMemcpyHostToDevice, h->stream));
@@ -282,6 +362,13 @@ StepArgs step_args(ifdlbm_s* h)
     return a;
 }
 
+hipError_t launch_items(int shape, int prec, bool impl, const StepArgs& a, const StripItem* items, int w0, int nw,
+                        bool residual, hipStream_t s)
+{
+    return shape == kMarch ? launch_fused_step(prec, impl, a, items, w0, nw, residual, s)
+                           : launch_tile_step(shape, prec, impl, a, items, w0, nw, residual, s);
+}
+
 // Enqueue one time step of the running cavities, reading buffer `cur`;
 // `local` numbers the step within its call or graph (stochastic rounding).
 int enqueue_step(ifdlbm_s* h, bool residual, uint32_t local)
@@ -294,12 +381,14 @@ int enqueue_step(ifdlbm_s* h, bool residual, uint32_t local)
     hipError_t e = hipSuccess;
     if (h->opt.batched) {
         e = staged ? launch_staged_step(prec, a, h->d_act_blocks, 0, (int)h->act_blocks.size(), residual, h->stream)
-                   : launch_fused_step(prec, impl, a, h->d_act_sorted, 0, (int)h->act_sorted.size(), residual, h->stream);
+                   : launch_items(h->cav_shape[h->act_items.empty() ? 0 : h->act_items[0].cav], prec, impl, a,
+                                  h->d_act_sorted, 0, (int)h->act_sorted.size(), residual, h->stream);
     } else {
         for (int c = 0; c < h->n_cav && e == hipSuccess; ++c) {
             if (!h->unit_count[c]) continue;
             e = staged ? launch_staged_step(prec, a, h->d_act_blocks, h->unit_first[c], h->unit_count[c], residual, h->stream)
-                       : launch_fused_step(prec, impl, a, h->d_act_items, h->unit_first[c], h->unit_count[c], residual, h->stream);
+                       : launch_items(h->cav_shape[c], prec, impl, a, h->d_act_items, h->unit_first[c], h->unit_count[c],
+                                      residual, h->stream);
         }
     }
     if (e == hipSuccess && residual)
@@ -486,18 +575,6 @@ void free_all(ifdlbm_s* h)
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
 }
 
-template <typename P>
-int dalloc(P** p, size_t bytes)
-{
-    hipError_t e = hipMalloc(reinterpret_cast<void**>(p), std::max<size_t>(bytes, 256));
-    if (e != hipSuccess) {
-        *p = nullptr;
-        return fail(e == hipErrorOutOfMemory ? IFDLBM_ENOMEM : IFDLBM_EDEVICE,
-                    std::string("hipMalloc(") + std::to_string(bytes) + "): " + hipGetErrorString(e));
-    }
-    return IFDLBM_OK;
-}
-
 }  // namespace
 
 extern "C" {
@@ -587,7 +664,7 @@ static int ifdlbm_create_impl(const ifdlbm_cavity* cav, int32_t n_cav, const ifd
     // layout and FP64 metric terms (Eqs. 3.2-3.8.2)
     std::vector<double> geo;
     int64_t f_off = 0, l_off = 0, max_nodes = 0;
-    size_t n_items = 0, n_blocks = 0;
+    size_t n_blocks = 0;
     for (int c = 0; c < n_cav; ++c) {
         const ifdlbm_cavity& v = cav[c];
         CavityDesc& d = h->desc[c];
@@ -627,14 +704,12 @@ static int ifdlbm_create_impl(const ifdlbm_cavity* cav, int32_t n_cav, const ifd
         const int64_t nn = (int64_t)d.nx * d.ny;
         max_nodes = std::max(max_nodes, nn);
         n_blocks += (size_t)((nn + kNodeBlock - 1) / kNodeBlock);
-        n_items += (size_t)ceil_div(d.ny, kMinSegRows) * ceil_div(d.nx, kStripOut);
         h->all_first.push_back((int32_t)h->all_blocks.size());
         for (int n = 0; n < nn; n += kNodeBlock) h->all_blocks.push_back({c, n});
         h->all_count.push_back((int32_t)h->all_blocks.size() - h->all_first.back());
     }
     h->f_elems = (size_t)f_off;
     h->l_elems = (size_t)l_off;
-    h->max_units = o.kernel == IFDLBM_KERNEL_STAGED ? n_blocks : n_items;
     h->scratch_elems = (size_t)max_nodes * 10;
 
     const int prec = o.precision;
@@ -654,12 +729,8 @@ static int ifdlbm_create_impl(const ifdlbm_cavity* cav, int32_t n_cav, const ifd
     }
     if (!rc) rc = dalloc(&h->d_all_blocks, h->all_blocks.size() * sizeof(NodeBlock));
     if (!rc) rc = dalloc(&h->d_act_blocks, n_blocks * sizeof(NodeBlock));
-    if (!rc) rc = dalloc(&h->d_act_items, n_items * sizeof(StripItem));
-    // per-XCD queues are padded to equal length: at most n_items * kXcds entries
-    if (!rc) rc = dalloc(&h->d_act_sorted, n_items * kXcds * sizeof(StripItem));
     if (!rc) rc = dalloc(&h->d_unit_first, n_cav * sizeof(int32_t));
     if (!rc) rc = dalloc(&h->d_unit_count, n_cav * sizeof(int32_t));
-    if (!rc) rc = dalloc(&h->d_partial, h->max_units * kPartials * sizeof(double));
     if (!rc) rc = dalloc(&h->d_res, (size_t)n_cav * kResult * sizeof(double));
     if (!rc) rc = dalloc(&h->d_ref, (size_t)n_cav * 2 * sizeof(double));
     if (!rc) rc = dalloc(&h->d_scratch, h->scratch_elems * sizeof(double));
@@ -944,15 +1015,21 @@ static int ifdlbm_autotune_impl(ifdlbm_t* h, int32_t steps_per_trial, int32_t* s
         return e;
     };
     if (!rc && save() != hipSuccess) rc = fail(IFDLBM_EDEVICE, "autotune: state backup");
-    int best = 0;
+    int best = 0;       // rows per item of the fastest kernel, and the option that selects it (0: the automatic tile)
+    int32_t best_opt = rows0;
     float best_ms = 0.0f;
     const int rec_every = h->rec_every;
     h->rec_every = 0;   // trials take no probe samples
     int max_ny = 0;
     for (int c = 0; c < h->n_cav; ++c) max_ny = std::max(max_ny, h->desc[c].ny);
-    for (int seg : kSegCandidates) {
+    std::vector<int32_t> trials;
+    for (int seg : kSegCandidates)
+        if (seg <= max_ny || seg == kSegCandidates[sizeof(kSegCandidates) / sizeof(kSegCandidates[0]) - 1]) trials.push_back(seg);
+    h->opt.segment_rows = 0;
+    const int tile = choose_kernel(h);
+    if (tile != kMarch && h->opt.batched) trials.push_back(0);
+    for (int32_t seg : trials) {
         if (rc) break;
-        if (seg > max_ny && seg != kSegCandidates[sizeof(kSegCandidates) / sizeof(kSegCandidates[0]) - 1]) continue;
         h->opt.segment_rows = seg;
         rc = rebuild_worklists(h);
         if (!rc) rc = eager_steps(h, 1);   // warm-up
@@ -963,13 +1040,14 @@ static int ifdlbm_autotune_impl(ifdlbm_t* h, int32_t steps_per_trial, int32_t* s
         float ms = 0.0f;
         if (!rc && hipEventElapsedTime(&ms, e0, e1) != hipSuccess) rc = fail(IFDLBM_EDEVICE, "hipEventElapsedTime");
         if (!rc && (best == 0 || ms < best_ms)) {
-            best = seg;
+            best = seg ? seg : kTileRows[tile];
+            best_opt = seg;
             best_ms = ms;
         }
         if (!rc && restore() != hipSuccess) rc = fail(IFDLBM_EDEVICE, "autotune: state restore");
     }
     h->rec_every = rec_every;
-    h->opt.segment_rows = rc ? rows0 : best;
+    h->opt.segment_rows = rc ? rows0 : best_opt;
     int rc2 = rebuild_worklists(h);
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);

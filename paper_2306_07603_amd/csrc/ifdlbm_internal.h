@@ -82,6 +82,14 @@ hipError_t launch_staged_step(int prec, const StepArgs& a, const NodeBlock* bloc
 hipError_t launch_fused_step(int prec, bool implicit_lambda, const StepArgs& a, const StripItem* items, int w0, int nw,
                              bool residual, hipStream_t s);
 
+// Fused schedule, small batches: one workgroup per tile of output nodes (step_tile.hip).  Shape s holds tiles of at
+// most kTileCols[s] x kTileRows[s] outputs.
+constexpr int kTileShapes = 3;
+constexpr int kTileCols[kTileShapes] = {8, 24, 24};
+constexpr int kTileRows[kTileShapes] = {8, 8, 24};
+hipError_t launch_tile_step(int shape, int prec, bool implicit_lambda, const StepArgs& a, const StripItem* items, int w0,
+                            int nw, bool residual, hipStream_t s);
+
 // Step (1) on every node of the listed blocks.
 hipError_t launch_init(int prec, void* f, void* l, const CavityDesc* desc, const NodeBlock* blocks, int nb,
                        hipStream_t s);

@@ -231,6 +231,11 @@ template <> struct Storage<P_FP16DEV> {
 __host__ __device__ constexpr int cxk(int k) { return k == 1 || k == 5 || k == 8 ? 1 : (k == 3 || k == 6 || k == 7 ? -1 : 0); }
 __host__ __device__ constexpr int cyk(int k) { return k == 2 || k == 5 || k == 6 ? 1 : (k == 4 || k == 7 || k == 8 ? -1 : 0); }
 
+// a b + c in one rounding (a general a * b + c for the derivative types).
+template <typename T> __device__ __forceinline__ T fused(T a, T b, T c) { return a * b + c; }
+template <> __device__ __forceinline__ float fused<float>(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+template <> __device__ __forceinline__ double fused<double>(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 // Eqs. (2.10)-(2.11) on deviations: u = sum c_k g_k and
 // P = (c_s^2 / omegabar_0) (-sum_{k>0} g_k + omega_0 |u|^2 / (2 c_s^2)) = 0.6 s - 0.4 |u|^2.
 template <typename T>
@@ -239,7 +244,7 @@ __device__ __forceinline__ void moments(const T g[9], T& P, T& ux, T& uy)
     ux = (g[1] - g[3]) + (g[5] - g[6]) - (g[7] - g[8]);
     uy = (g[2] - g[4]) + (g[5] + g[6]) - (g[7] + g[8]);
     const T s = ((g[1] + g[2]) + (g[3] + g[4])) + ((g[5] + g[6]) + (g[7] + g[8]));
-    P = T(0.6) * s - T(0.4) * (ux * ux + uy * uy);
+    P = fused(T(0.6), s, T(-0.4) * fused(ux, ux, uy * uy));
 }
 
 // Eq. (2.8) minus omega_k rho0, with the second-order term over 2 c_s^4:
@@ -248,73 +253,48 @@ __device__ __forceinline__ void moments(const T g[9], T& P, T& ux, T& uy)
 // a (2 a + 2): every constant of that form is an inline operand of the FP64
 // FMA (3 and 4.5 are not, and VOP3 takes no literal), and c.u of a lattice
 // direction is a signed sum of a_x = 1.5 u_x and a_y = 1.5 u_y, so no product
-// with a zero velocity component is formed.  equilibrium_k is the same
-// arithmetic population by population.
+// with a zero velocity component is formed.  e_k is only ever used in a sum:
+// the product with omega_k is fused into it.  The fused multiply-adds are
+// written out and the step sources are compiled with contraction limited to
+// single expressions, so that every kernel rounds a node the same way.
 template <typename T>
-__device__ __forceinline__ T eq_velocity_term(T cu)   // FP32: 3 c.u + 4.5 (c.u)^2
-{
-    return cu * (T(3) + T(4.5) * cu);
-}
-__device__ __forceinline__ double eq_velocity_term_a(double a)   // FP64: a = 1.5 c.u
-{
-    return a * __builtin_fma(a, 2.0, 2.0);
-}
-
-// a = 1.5 c_k.u of population k (FP64) from a_x = 1.5 u_x and a_y = 1.5 u_y
-__device__ __forceinline__ double eq_a(int k, double ax, double ay)
-{
-    switch (k) {
-    case 1: return ax;
-    case 2: return ay;
-    case 3: return -ax;
-    case 4: return -ay;
-    case 5: return ax + ay;
-    case 6: return ay - ax;
-    case 7: return -(ax + ay);
-    default: return ax - ay;
+struct Equilibrium {
+    T base, e0, x, y;   // x, y: the velocity, 1.5 times it in FP64
+    __device__ __forceinline__ Equilibrium(T P, T ux, T uy)
+    {
+        const T uu = fused(ux, ux, uy * uy);
+        base = fused(T(3), P, T(-1.5) * uu);
+        e0 = fused(T(-5) / T(3), P, T(-2) / T(3) * uu);
+        if constexpr (std::is_same<T, double>::value) {
+            x = __builtin_fma(0.5, ux, ux);
+            y = __builtin_fma(0.5, uy, uy);
+        } else {
+            x = ux;
+            y = uy;
+        }
     }
-}
+    __device__ static constexpr double w(int k) { return k < 5 ? 1.0 / 9.0 : 1.0 / 36.0; }
+    // e_k / omega_k, k > 0
+    __device__ __forceinline__ T q(int k) const
+    {
+        const T c = k == 1 ? x : k == 2 ? y : k == 3 ? -x : k == 4 ? -y : k == 5 ? x + y : k == 6 ? y - x : k == 7 ? -(x + y) : x - y;
+        if constexpr (std::is_same<T, double>::value)
+            return __builtin_fma(c, __builtin_fma(c, 2.0, 2.0), base);
+        else
+            return fused(c, fused(T(4.5), c, T(3)), base);
+    }
+    __device__ __forceinline__ T value(int k) const { return k == 0 ? e0 : T(w(k)) * q(k); }
+    __device__ __forceinline__ T plus(int k, T v) const { return k == 0 ? e0 + v : fused(T(w(k)), q(k), v); }     // e_k + v
+    __device__ __forceinline__ T minus(int k, T v) const { return k == 0 ? e0 - v : fused(T(w(k)), q(k), -v); }   // e_k - v
+    __device__ __forceinline__ T from(int k, T v) const { return k == 0 ? v - e0 : fused(T(-w(k)), q(k), v); }    // v - e_k
+};
 
 template <typename T>
 __device__ __forceinline__ void equilibrium(T P, T ux, T uy, T e[9])
 {
-    const T uu = ux * ux + uy * uy;
-    const T base = T(3) * P - T(1.5) * uu;
-    const T w1 = T(1) / T(9), w5 = T(1) / T(36);
-    e[0] = T(-5) / T(3) * P - T(2) / T(3) * uu;
-    if constexpr (std::is_same<T, double>::value) {
-        const double ax = __builtin_fma(0.5, ux, ux), ay = __builtin_fma(0.5, uy, uy);
+    const Equilibrium<T> eq(P, ux, uy);
 #pragma unroll
-        for (int k = 1; k < 9; ++k) e[k] = (k < 5 ? w1 : w5) * (base + eq_velocity_term_a(eq_a(k, ax, ay)));
-    } else {
-        auto q = [&](T cu) { return base + eq_velocity_term(cu); };
-        e[1] = w1 * q(ux);
-        e[2] = w1 * q(uy);
-        e[3] = w1 * q(-ux);
-        e[4] = w1 * q(-uy);
-        e[5] = w5 * q(ux + uy);
-        e[6] = w5 * q(uy - ux);
-        e[7] = w5 * q(-ux - uy);
-        e[8] = w5 * q(ux - uy);
-    }
-}
-
-// Population k of Eq. (2.8) alone (same arithmetic as equilibrium()).
-template <typename T>
-__device__ __forceinline__ T equilibrium_k(T P, T ux, T uy, int k)
-{
-    const T uu = ux * ux + uy * uy;
-    const T base = T(3) * P - T(1.5) * uu;
-    const T w = k < 5 ? T(1) / T(9) : T(1) / T(36);
-    if (k == 0) return T(-5) / T(3) * P - T(2) / T(3) * uu;
-    if constexpr (std::is_same<T, double>::value) {
-        const double ax = __builtin_fma(0.5, ux, ux), ay = __builtin_fma(0.5, uy, uy);
-        return w * (base + eq_velocity_term_a(eq_a(k, ax, ay)));
-    } else {
-        const T cu = k == 1 ? ux : k == 2 ? uy : k == 3 ? -ux : k == 4 ? -uy
-                   : k == 5 ? ux + uy : k == 6 ? uy - ux : k == 7 ? -ux - uy : ux - uy;
-        return w * (base + eq_velocity_term(cu));
-    }
+    for (int k = 0; k < 9; ++k) e[k] = eq.value(k);
 }
 
 // 1/x for x > 0: v_rcp_f32 (1 ulp) in FP32; v_rcp_f64 refined by two Newton
@@ -599,12 +579,66 @@ __device__ __forceinline__ void inward(int i, int j, int nx, int ny, int& ni, in
 template <typename T>
 __device__ __forceinline__ void extrapolate(const T xnb[9], T uwall, T xb[9])
 {
-    T P, ux, uy, e_nb[9], e_w[9];
+    T P, ux, uy;
     moments(xnb, P, ux, uy);
-    equilibrium(P, ux, uy, e_nb);
-    equilibrium(P, uwall, T(0), e_w);
+    const Equilibrium<T> nb(P, ux, uy), wall(P, uwall, T(0));
 #pragma unroll
-    for (int k = 0; k < 9; ++k) xb[k] = e_w[k] + (xnb[k] - e_nb[k]);
+    for (int k = 0; k < 9; ++k) xb[k] = wall.plus(k, nb.from(k, xnb[k]));
+}
+
+// ------------------------------------------------ stages of a node
+// Shared by the kernels of the fused schedule, so that they store the same bits.
+
+// Stage A: Steps (2)-(4) of one node from its stored g and lambda: lambda of
+// this step, f-bar+ (Eq. 2.16) and f-hat+ (Eq. 2.15); with the exact final
+// update (FP32SRF) hp is only the collision increment of f-hat+, the stored g
+// is added in FP64 at stage C.
+template <typename S, bool IMPL>
+__device__ __forceinline__ void collide(const typename S::T (&g)[9], typename S::V lam_old, const PowerLaw<typename S::V>& pl,
+                                        typename S::T (&bp)[9], typename S::T (&hp)[9], typename S::V& lam)
+{
+    using T = typename S::T;
+    using V = typename S::V;
+    T d[9];
+    if constexpr (S::kExactFinal) {
+        // e - g in FP64 from the exact stored g: at low shear the non-equilibrium part is far below an FP32 ulp of
+        // g, and Step (2) raises it to the power (n - 1) / 2.  The second moments of Step (2) come from the FP32
+        // values of e - g: their sums need FP32 accuracy only, as the power law and the relaxation coefficients
+        // are FP32 in this mode.
+        double gd[9], P, ux, uy;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) gd[k] = (double)g[k];
+        moments(gd, P, ux, uy);
+        const Equilibrium<double> eq(P, ux, uy);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) d[k] = T(eq.minus(k, gd[k]));
+    } else {
+        T P, ux, uy;
+        moments(g, P, ux, uy);
+        const Equilibrium<T> eq(P, ux, uy);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) d[k] = eq.minus(k, g[k]);
+    }
+    lam = relaxation_time_d<IMPL>(d, lam_old, pl);
+    const Relax<V> rx(lam, pl.dt);
+    const T b_hat = T(rx.b_hat), b_bar = T(rx.b_bar);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        bp[k] = fused(b_bar, d[k], g[k]);
+        hp[k] = S::kExactFinal ? b_hat * d[k] : fused(b_hat, d[k], g[k]);
+    }
+}
+
+// Eq. (2.17): f(t + dt/2) from f-bar.
+template <typename T, typename V>
+__device__ __forceinline__ void half_step(const T (&fb)[9], V lam, V dt, T (&out)[9])
+{
+    T P, ux, uy;
+    moments(fb, P, ux, uy);
+    const Equilibrium<T> eq(P, ux, uy);
+    const T b = T(half_coef(lam, dt));
+#pragma unroll
+    for (int k = 0; k < 9; ++k) out[k] = fused(b, eq.minus(k, fb[k]), fb[k]);
 }
 
 }  // namespace ifd

@@ -34,6 +34,7 @@
 // resource per array and cavity, the plane of population k as a scalar
 // offset, the row and column as one 32-bit vector offset.
 #include "ifdlbm_internal.h"
+#include "step_common.h"
 
 namespace ifd {
 namespace {
@@ -110,36 +111,6 @@ template <typename T> __device__ __forceinline__ const T* geo_of(const StepArgs&
 template <> __device__ __forceinline__ const double* geo_of<double>(const StepArgs& a) { return a.geo; }
 template <> __device__ __forceinline__ const float* geo_of<float>(const StepArgs& a) { return a.geo32; }
 
-// Weights of Eq. (2.5) times sign(c) * 2h on the upwind-sorted points a2
-// (two behind), a1 (one behind), c0 and f1 (one ahead):
-// sign(c) * central = f1 - a1 (Eq. 2.6), sign(c) * upwind = 3 c0 - 4 a1 + a2
-// (Eq. 2.7), so eps * central + (1 - eps) * upwind is
-// eps f1 - (4 - 3 eps) a1 + 3 (1 - eps) c0 + (1 - eps) a2.
-template <typename T>
-struct MixedWeights {
-    T wf, wa1, wc, wa2;
-    __device__ __forceinline__ MixedWeights(T eps, T scale)
-        : wf(scale * eps), wa1(-scale * (T(4) - T(3) * eps)), wc(scale * T(3) * (T(1) - eps)),
-          wa2(scale * (T(1) - eps))
-    {
-    }
-    __device__ __forceinline__ T apply(T a2, T a1, T c0, T f1) const { return ((wc * c0 + wa1 * a1) + wa2 * a2) + wf * f1; }
-    // The same on differences, which FP32 arithmetic needs: neighbouring
-    // values agree to many digits, so the weighted sum of the values above
-    // loses to cancellation what differences keep (an error of order one ulp
-    // of f per step that does not average out over a steady run).  With the
-    // backward differences B(m) = x(m) - x(m - 1) along the upwind direction,
-    // n = B at the point (c0 - a1), f = B one further upwind (a1 - a2) and
-    // o = B one downwind (f1 - a1 = n + o), it is
-    // (eps + 3 (1 - eps)) n - (1 - eps) f + eps o.
-    __device__ __forceinline__ T apply_back(T n, T f, T o) const { return ((wc + wf) * n - wa2 * f) + wf * o; }
-    // r minus the same, as three multiply-adds into r
-    __device__ __forceinline__ T sub_back(T r, T n, T f, T o) const
-    {
-        return __builtin_fmaf(-(wc + wf), n, __builtin_fmaf(wa2, f, __builtin_fmaf(-wf, o, r)));
-    }
-};
-
 // x of lane l - 1 in lane l (lane 0 reads 0): a wavefront shift of the data-parallel primitives, folded by the
 // compiler into the instruction that uses it.
 __device__ __forceinline__ float lane_below(float x)
@@ -147,9 +118,6 @@ __device__ __forceinline__ float lane_below(float x)
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x138 /* wave_shr:1 */,
                                                                 0xF, 0xF, true));
 }
-
-// Mixed differences from differences first where the distributions are FP32.
-template <typename T> constexpr bool kDiffForm = sizeof(T) == 4;
 
 // Population k of the eta direction moves up (c_ky > 0: 2, 5, 6), down
 // (c_ky < 0: 4, 7, 8) or not at all (0, 1, 3).
@@ -275,38 +243,6 @@ __device__ __forceinline__ void wall_source(T (*w)[9], int i, int nx, const T (&
     for (int k = 0; k < 9; ++k) src[k] = interior ? own[k] : w[side][k];
 }
 
-template <typename T, typename V>
-__device__ __forceinline__ void half_step(const T (&fb)[9], V lam, V dt, T (&out)[9])
-{
-    T P, ux, uy, e[9];
-    moments(fb, P, ux, uy);
-    equilibrium(P, ux, uy, e);
-    const T b = T(half_coef(lam, dt));
-#pragma unroll
-    for (int k = 0; k < 9; ++k) out[k] = fb[k] + b * (e[k] - fb[k]);
-}
-
-// Eq. (2.19) sums of one node (the layout of kPartials); ref holds the
-// cavity's shifts r_d, r_p.
-template <typename T>
-__device__ __forceinline__ void residual_add(const T (&gn)[9], const T (&old)[3], const double (&ref)[2],
-                                             double (&acc)[kPartials])
-{
-    T P, ux, uy;
-    moments(gn, P, ux, uy);
-    const double du = (double)ux - (double)old[1], dv = (double)uy - (double)old[2], dp = (double)P - (double)old[0];
-    const double sd = dp - ref[0], sp = (double)P - ref[1];
-    acc[0] += du * du + dv * dv;
-    acc[1] += (double)ux * ux + (double)uy * uy;
-    acc[2] += dp * dp;
-    acc[3] += (double)P * P;
-    acc[4] += sd;
-    acc[5] += sp;
-    acc[6] += (isfinite((double)ux) && isfinite((double)uy) && isfinite((double)P)) ? 0.0 : 1.0;
-    acc[7] += sd * sd;
-    acc[8] += sp * sp;
-}
-
 // One work item.  Register ring slot of row t - d at unrolled phase R:
 // (R + 5 - d) % 5 for f-bar+ and lambda (d = 0..4), (R + 10 - d) % 5 for
 // f(t + dt/2) (d = 2..6); with one row per trip R is 0 and the rings move.
@@ -331,7 +267,6 @@ struct March {
     int lane, nx, ny, i, ic, j0, j1, qlo, qhi, t_begin, t_last;
     bool out_col, walls_b, walls_c;
     PowerLaw<V> pl;
-    V dtv;
     T ulid, sx_b, sy_b, sx_c, sy_c;
     T eps;
     // the row metric a_j, read-only while a step runs: through the constant address space a row's value
@@ -376,7 +311,6 @@ struct March {
         j1 = it.j1;
         qlo = max(j0 - 2, 0);
         qhi = min(j1 + 1, ny - 1);
-        dtv = V(c.dt);
         const T dt = T(c.dt);
         ulid = T(c.u_lid);
         sy_b = T(0.5) * dt * T(c.inv2deta);
@@ -605,7 +539,7 @@ struct March {
         // ------------------------------------------------------------ A: row t
         if (t <= ny - 1) {
             const int hs = hslot(t);
-            T g[9], e[9], d[9], P, ux, uy;
+            T g[9];
 #pragma unroll
             for (int k = 0; k < 9; ++k) g[k] = S::cvt(gn_[k], k);
             const V lam_old = V(ln_);
@@ -621,36 +555,11 @@ struct March {
             }
             if (fetch_next) fetch(t + 1);   // consumed by the next row (ten vector-memory loads)
             V l;
-            if constexpr (S::kExactFinal) {
-                // e - g in FP64 from the exact stored g: at low shear the non-equilibrium part is far below
-                // an FP32 ulp of g, and Step (2) raises it to the power (n - 1) / 2
-                double gd[9], dd[9], Pd, uxd, uyd;
-#pragma unroll
-                for (int k = 0; k < 9; ++k) gd[k] = (double)g[k];
-                moments(gd, Pd, uxd, uyd);
-#pragma unroll
-                for (int k = 0; k < 9; ++k) {
-                    dd[k] = equilibrium_k(Pd, uxd, uyd, k) - gd[k];
-                    d[k] = T(dd[k]);
-                }
-                // the second moments of Step (2) from the FP32 values of e - g: their sums need FP32 accuracy
-                // only, as the power law and the relaxation coefficients are FP32 in this mode
-                l = relaxation_time_d<IMPL>(d, lam_old, pl);
-            } else {
-                moments(g, P, ux, uy);
-                equilibrium(P, ux, uy, e);
-#pragma unroll
-                for (int k = 0; k < 9; ++k) d[k] = e[k] - g[k];
-                l = relaxation_time_d<IMPL>(d, lam_old, pl);
-            }
-            const Relax<V> rx(l, dtv);
-            const T b_hat = T(rx.b_hat), b_bar = T(rx.b_bar);
+            T hp[9];
+            collide<S, IMPL>(g, lam_old, pl, gbp[sg(R, 0)], hp, l);
 #pragma unroll
             for (int k = 0; k < 9; ++k) {
-                gbp[sg(R, 0)][k] = g[k] + b_bar * d[k];
-                // exact final update: only the collision increment of f-hat+ (Eq. 2.15); the stored g is added
-                // in FP64 at stage C
-                sh.hp[hs][k][lane] = S::kExactFinal ? b_hat * d[k] : g[k] + b_hat * d[k];
+                sh.hp[hs][k][lane] = hp[k];
                 if constexpr (S::kExactFinal) {
                     if (k < kGxRing) sh.gr[hs][k][lane] = g[k];
                 }
@@ -684,7 +593,7 @@ struct March {
                     T src[9], fb0[9], out0[9];
                     wall_source(sh.wb, i, nx, fb, src);
                     extrapolate(src, T(0), fb0);
-                    half_step(fb0, lam[sg(R, 3)], dtv, out0);
+                    half_step(fb0, lam[sg(R, 3)], pl.dt, out0);
 #pragma unroll
                     for (int k = 0; k < 9; ++k) fh[sf(R, 3)][k] = out0[k];
                 }
@@ -703,7 +612,7 @@ struct March {
             }
             if (q >= 1) {
                 T out[9];
-                half_step(fb, lam[sg(R, 2)], dtv, out);
+                half_step(fb, lam[sg(R, 2)], pl.dt, out);
 #pragma unroll
                 for (int k = 0; k < 9; ++k) fh[sf(R, 2)][k] = out[k];
             }

@@ -86,9 +86,10 @@ __global__ __launch_bounds__(kNodeBlock) void k_stage_a(StepArgs a, const NodeBl
 #pragma unroll
         for (int k = 0; k < 9; ++k) gd[k] = (double)g[k];
         moments(gd, Pd, uxd, uyd);
+        const Equilibrium<double> eq(Pd, uxd, uyd);
 #pragma unroll
         for (int k = 0; k < 9; ++k) {
-            dd[k] = equilibrium_k(Pd, uxd, uyd, k) - gd[k];
+            dd[k] = eq.minus(k, gd[k]);
             d[k] = T(dd[k]);
         }
         lam = pl.implicit ? relaxation_time_d<true>(dd, V(l[c.l_off + r.id]), pl)
