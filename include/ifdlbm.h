@@ -265,9 +265,9 @@ int ifdlbm_gradient_noalloc(const ifdlbm_cavity* cav, const ifdlbm_options* opt,
    dt_rule and hip_stream apply; lambda_mode must be LAGGED) keeps the state every checkpoint_every steps; the
    reverse sweep recomputes each segment from its checkpoint and walks it backwards through the transposed
    Steps (2)-(6) of Section 4 in FP64, accumulating the parameter adjoints in FP64.  With an FP32 storage mode
-   the gradient is that of the FP64 step linearised about the FP32 trajectory.  Device memory: the raw state
-   once per checkpoint, (min(checkpoint_every, n_steps) + 1) FP64 states of 10 doubles per node, and about
-   60 doubles per node of work arrays, allocated and freed inside the call, which synchronises the stream.
+   the gradient is that of the FP64 step linearised about the FP32 trajectory.  Device memory: the stored state
+   once per checkpoint and once per step of a segment (min(checkpoint_every, n_steps) + 1), and about 20 doubles
+   per node of work arrays, in one allocation made and freed inside the call, which synchronises the stream.
    Errors: EINVAL, ENOMEM, EDEVICE, EDIVERGED (non-finite trajectory or adjoint). */
 int ifdlbm_adjoint(const ifdlbm_cavity* cav, const ifdlbm_options* opt, int64_t n_steps, int32_t checkpoint_every,
                    int32_t objective, double* J, double grad[3]);

@@ -24,7 +24,8 @@
 // times x's adjoint; the wall extrapolation is transposed the same way, the
 // inward node collecting from the wall nodes that copy it.  The forward
 // quantities a step needs (f-bar+, lambda, f-bar, f(t + dt/2)) are recomputed
-// from the stored state at t, in FP64.
+// from the stored state at t, in FP64.  All stages of a step run in one kernel
+// over tiles of nodes with their halo.
 //
 // Parameter adjoints are accumulated as those of the primitive quantities:
 // cot(theta) through the metric terms a_j = 1/(1 + 2 eta_j cot), s_i = cot
@@ -35,6 +36,7 @@
 // kernel reduces them per block into its own slot of a running FP64 sum, so
 // the result does not depend on scheduling.
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 #include "ifdlbm_internal.h"
@@ -48,10 +50,11 @@ constexpr int kB = 256;   // threads per block
 // accumulators of the primitive parameter adjoints
 enum Acc { A_COT = 0, A_DT, A_K3, A_EXPO, A_ULID, A_LAM0, A_N };
 // one slot of block sums per kernel that contributes
-enum Slot { S_OBJ = 0, S_CB, S_C, S_BH, S_BH2, S_B, S_A, S_INIT, S_N };
+enum Slot { S_OBJ = 0, S_STEP, S_INIT, S_N };
 
 struct AdjParams {
-    int nx, ny;
+    int nx, ny, pitch;
+    int64_t plane;       // of a stored state
     double dt, K3, expo, g2min, mix, ulid, inv2dxi, inv2deta, dxi, deta;
     const double* geo;   // a_j [ny], s_i [nx], d a_j / d cot [ny], d s_i / d cot [nx]
     double* acc;         // [S_N][blocks][A_N]
@@ -161,140 +164,14 @@ __device__ __forceinline__ double stencil_weight(int o, bool pos, bool lo, bool 
     }
 }
 
-__device__ __forceinline__ double c_xi(const AdjParams& p, int i, int j, int k)
+// The q-th of the wall nodes that may extrapolate from the interior node (i, j): the edge node on the side wall, the
+// one on the bottom or lid, and the corner.  False where the node is not next to that wall.
+__device__ __forceinline__ bool wall_of(const AdjParams& p, int i, int j, int q, int& wi, int& wj)
 {
-    return p.geo[j] * ((double)cxk(k) - (double)cyk(k) * p.geo[p.ny + i]);
-}
-
-// d c_k,xi / d cot at (i, j).
-__device__ __forceinline__ double c_xi_dcot(const AdjParams& p, int i, int j, int k)
-{
-    return p.geo[p.ny + p.nx + j] * ((double)cxk(k) - (double)cyk(k) * p.geo[p.ny + i]) -
-           p.geo[j] * (double)cyk(k) * p.geo[2 * p.ny + p.nx + i];
-}
-
-// Forward pieces of S_k[phi](x) at interior x: M_xi * inv2dxi and M_eta * inv2deta.
-__device__ __forceinline__ void stencil_parts(const AdjParams& p, const double* plane, int i, int j, int k, double& mxi,
-                                              double& meta)
-{
-    const bool pos = c_xi(p, i, j, k) >= 0.0;
-    mxi = 0.0;
-    for (int o = -2; o <= 2; ++o) {
-        const double w = stencil_weight(o, pos, i == 1, i == p.nx - 2, p.mix);
-        if (w != 0.0) mxi += w * plane[at(p, i + o, j)];
-    }
-    mxi *= p.inv2dxi;
-    meta = 0.0;
-    const int cy = cyk(k);
-    if (cy != 0)
-        for (int o = -2; o <= 2; ++o) {
-            const double w = stencil_weight(o, cy > 0, j == 1, j == p.ny - 2, p.mix);
-            if (w != 0.0) meta += w * plane[at(p, i, j + o)];
-        }
-    meta *= p.inv2deta;
-}
-
-// Transposed stencil at m = (i, j): sum over interior x reading m of
-// ybar(x) * (weight x gives to m in S_k).
-__device__ __forceinline__ double stencil_t(const AdjParams& p, const double* ybar_plane, int i, int j, int k)
-{
-    double acc = 0.0;
-    if (j >= 1 && j <= p.ny - 2)
-        for (int o = -2; o <= 2; ++o) {
-            const int ix = i - o;
-            if (ix < 1 || ix > p.nx - 2) continue;
-            const double c = c_xi(p, ix, j, k);
-            const double w = stencil_weight(o, c >= 0.0, ix == 1, ix == p.nx - 2, p.mix);
-            if (w != 0.0) acc += ybar_plane[at(p, ix, j)] * c * w * p.inv2dxi;
-        }
-    const int cy = cyk(k);
-    if (cy != 0 && i >= 1 && i <= p.nx - 2)
-        for (int o = -2; o <= 2; ++o) {
-            const int jx = j - o;
-            if (jx < 1 || jx > p.ny - 2) continue;
-            const double w = stencil_weight(o, cy > 0, jx == 1, jx == p.ny - 2, p.mix);
-            if (w != 0.0) acc += ybar_plane[at(p, i, jx)] * (double)cy * w * p.inv2deta;
-        }
-    return acc;
-}
-
-// Wall nodes whose inward neighbour is the interior node (i, j): at most three
-// (an edge node on each adjacent wall and the diagonal corner).
-__device__ __forceinline__ int walls_of(const AdjParams& p, int i, int j, int (&wi)[3], int (&wj)[3])
-{
-    int n = 0;
-    const int di = i == 1 ? -1 : (i == p.nx - 2 ? 1 : 0);
-    const int dj = j == 1 ? -1 : (j == p.ny - 2 ? 1 : 0);
-    if (di) { wi[n] = i + di; wj[n] = j; ++n; }
-    if (dj) { wi[n] = i; wj[n] = j + dj; ++n; }
-    if (di && dj) { wi[n] = i + di; wj[n] = j + dj; ++n; }
-    return n;
-}
-
-// ---------------------------------------------- forward recomputation (FP64)
-
-// Stage A: f-bar+ (9 planes) and lambda of the step from the state at t.
-__global__ __launch_bounds__(kB) void r_stage_a(AdjParams p, const double* st, double* bp, double* ln)
-{
-    int i, j;
-    if (!node_of(p, i, j)) return;
-    const int64_t id = at(p, i, j), pl = (int64_t)p.nx * p.ny;
-    double g[9], e[9], P, ux, uy;
-    for (int k = 0; k < 9; ++k) g[k] = st[k * pl + id];
-    moments(g, P, ux, uy);
-    equilibrium(P, ux, uy, e);
-    double n[9];
-    for (int k = 0; k < 9; ++k) n[k] = g[k] - e[k];
-    const double s58 = (n[5] + n[6]) + (n[7] + n[8]);
-    const double pxx = (n[1] + n[3]) + s58, pyy = (n[2] + n[4]) + s58, pxy = (n[5] - n[6]) + (n[7] - n[8]);
-    const double r = 1.0 / (2.0 * st[9 * pl + id] + p.dt);
-    const double gamma2 = 18.0 * (pxx * pxx + 2.0 * pxy * pxy + pyy * pyy) * r * r;
-    const double lam = p.K3 * pow(gamma2 > p.g2min ? gamma2 : p.g2min, p.expo);
-    const double bb = 1.5 * p.dt / (2.0 * lam + p.dt);
-    for (int k = 0; k < 9; ++k) bp[k * pl + id] = g[k] + bb * (e[k] - g[k]);
-    ln[id] = lam;
-}
-
-// Stage B: f-bar at interior nodes.
-__global__ __launch_bounds__(kB) void r_stage_b(AdjParams p, const double* bp, double* fb)
-{
-    int i, j;
-    if (!node_of(p, i, j) || !interior(p, i, j)) return;
-    const int64_t id = at(p, i, j), pl = (int64_t)p.nx * p.ny;
-    fb[id] = bp[id];
-    for (int k = 1; k < 9; ++k) {
-        double mxi, meta;
-        stencil_parts(p, bp + k * pl, i, j, k, mxi, meta);
-        fb[k * pl + id] = bp[k * pl + id] - 0.5 * p.dt * (c_xi(p, i, j, k) * mxi + (double)cyk(k) * meta);
-    }
-}
-
-__device__ __forceinline__ void half_input(const AdjParams& p, const double* fb, int i, int j, double x[9])
-{
-    const int64_t pl = (int64_t)p.nx * p.ny;
-    if (interior(p, i, j)) {
-        for (int k = 0; k < 9; ++k) x[k] = fb[k * pl + at(p, i, j)];
-        return;
-    }
-    int ni = i == 0 ? 1 : (i == p.nx - 1 ? p.nx - 2 : i);
-    int nj = j == 0 ? 1 : (j == p.ny - 1 ? p.ny - 2 : j);
-    double xnb[9];
-    for (int k = 0; k < 9; ++k) xnb[k] = fb[k * pl + at(p, ni, nj)];
-    extrapolate(xnb, j == p.ny - 1 ? p.ulid : 0.0, x);
-}
-
-// Stage BH: f(t + dt/2) at every node.
-__global__ __launch_bounds__(kB) void r_stage_bh(AdjParams p, const double* fb, const double* ln, double* fh)
-{
-    int i, j;
-    if (!node_of(p, i, j)) return;
-    const int64_t id = at(p, i, j), pl = (int64_t)p.nx * p.ny;
-    double x[9], e[9], P, ux, uy;
-    half_input(p, fb, i, j, x);
-    moments(x, P, ux, uy);
-    equilibrium(P, ux, uy, e);
-    const double hc = p.dt / (4.0 * ln[id] + p.dt);
-    for (int k = 0; k < 9; ++k) fh[k * pl + id] = x[k] + hc * (e[k] - x[k]);
+    const int di = i == 1 ? -1 : (i == p.nx - 2 ? 1 : 0), dj = j == 1 ? -1 : (j == p.ny - 2 ? 1 : 0);
+    wi = q == 1 ? i : i + di;
+    wj = q == 0 ? j : j + dj;
+    return (q == 1 || di) && (q == 0 || dj);
 }
 
 // ------------------------------------------------------- adjoint stages
@@ -334,174 +211,315 @@ __global__ __launch_bounds__(kB) void a_objective(AdjParams p, double cot, const
     accumulate(p, S_OBJ, v);
 }
 
-// CB^T: the adjoint G of the interior values of the new state, f-hat(t + dt)
-// before its walls are set: the state adjoint itself plus what the wall
-// nodes extrapolated from this node hand back.  st1 is the state at t + dt.
-__global__ __launch_bounds__(kB) void a_stage_cb(AdjParams p, const double* st1, const double* fbar, double* G)
+// One adjoint step of a tile of 12 x 12 nodes: from the adjoint of the state
+// at t + dt (fb_in, lb_in) to that of the state at t (fb_out, lb_out).  One
+// workgroup holds the tile and four more nodes on every side, one per thread,
+// and walks them through the forward stages and back, each stage's values in
+// LDS: a node's distance from the tile is at most 4 for A and CB^T, 2 for B,
+// BH, C^T, BH^T and the wall transpose (one more for the wall nodes next to
+// those), 0 for B^T and A^T.  Parameter adjoints are summed over the nodes of
+// the tile proper.
+// Bound by the chain of FP64 instructions of a thread (2330, with wall handling
+// 3560, at 8 to 10 cycles each with two wavefronts per SIMD): 17 us on 33 x 33
+// and 20 us on 129 x 129 nodes, where the nine launches of a stage each, through
+// HBM, took 105 us.  Tiles of 8 x 8 recompute more halo (50 against 45 us per
+// step of the whole adjoint on 129 x 129 before the walls' loops left their
+// arrays), tiles of 16 x 16 leave 168 registers per thread, which spill (59 us).
+constexpr int kTile = 12, kHalo = 4, kSide = kTile + 2 * kHalo;
+constexpr int kNodes = kSide * kSide, kThreads = (kNodes + kWaveLanes - 1) / kWaveLanes * kWaveLanes;
+
+struct AdjLds {
+    double bp[9][kNodes];   // f-bar+
+    // moving populations k = 1 .. 8 in plane k - 1
+    double fh[8][kNodes];   // f(t + dt/2)
+    double G[8][kNodes];    // adjoint of the new f-hat, then of f-bar
+    double X[8][kNodes];    // adjoint of the half-step input
+};
+
+// 2h times the mixed difference at a node from points `step` apart: eps * central + (1 - eps) * upwind on the points
+// sorted by the upwind side (a1 one behind, a2 two behind, f1 one ahead), without a branch; edge: the second upwind
+// point leaves the grid (first-order form, as with the linear ghost 2 a1 - c0).
+__device__ __forceinline__ double mixed_at(const double* x, int step, bool pos, bool edge, double eps)
 {
-    double v[A_N] = {};
-    int i, j;
-    if (node_of(p, i, j) && interior(p, i, j)) {
-        const int64_t id = at(p, i, j), pl = (int64_t)p.nx * p.ny;
-        double gb[9], x[9];
-        for (int k = 0; k < 9; ++k) {
-            gb[k] = fbar[k * pl + id];
-            x[k] = st1[k * pl + id];
+    const int u = pos ? -step : step;
+    const double c0 = x[0], a1 = x[u], f1 = x[-u], far = x[2 * u];
+    const double a2 = edge ? 2.0 * a1 - c0 : far;
+    const double m = eps * (f1 - a1) + (1.0 - eps) * (3.0 * c0 - 4.0 * a1 + a2);
+    return pos ? m : -m;
+}
+
+// Tiles [xa, xb) x [ya, yb) of the tx x ty ones keep clear of the walls and the nodes next to them: they take the
+// kernel without wall handling.  EDGE runs the frame around them, or every tile where that is one launch less.
+struct TileFrame {
+    int tx, ty, xa, xb, ya, yb;
+    __host__ __device__ int edge_tiles() const { return tx * ty - (xb - xa) * (yb - ya); }
+    __device__ void tile(bool edge, int b, int& x, int& y) const
+    {
+        const int w = xb - xa, h = yb - ya;
+        if (!edge) {
+            x = xa + b % w;
+            y = ya + b / w;
+            return;
         }
-        int wi[3], wj[3];
-        const int nw = walls_of(p, i, j, wi, wj);
-        for (int q = 0; q < nw; ++q) {
+        const int side = tx - w, mid = h * side;   // the rows below, beside and above the inner tiles
+        if (b < ya * tx || b >= ya * tx + mid) {
+            const int c = b < ya * tx ? b : b - mid + h * tx;
+            x = c % tx;
+            y = c / tx;
+            return;
+        }
+        const int c = b - ya * tx, q = c % side;
+        x = q < xa ? q : q + w;
+        y = ya + c / side;
+    }
+};
+
+template <int PREC, bool EDGE>
+__global__ __launch_bounds__(kThreads, 2) void k_adjoint_step(AdjParams p, TileFrame fr, const typename Storage<PREC>::F* st,
+                                                        const typename Storage<PREC>::L* lst,
+                                                        const typename Storage<PREC>::F* st1, const double* fb_in,
+                                                        const double* lb_in, double* fb_out, double* lb_out)
+{
+    using S = Storage<PREC>;
+    __shared__ AdjLds sh;
+    double v[A_N] = {};
+    int bx, by;
+    fr.tile(EDGE, (int)blockIdx.x, bx, by);
+    bx = __builtin_amdgcn_readfirstlane(bx);
+    by = __builtin_amdgcn_readfirstlane(by);
+    const int nx = p.nx, ny = p.ny, t = min((int)threadIdx.x, kNodes - 1), lx = t % kSide, ly = t / kSide;
+    const int i0 = bx * kTile, j0 = by * kTile;
+    const int i = i0 - kHalo + lx, j = j0 - kHalo + ly;
+    const bool grid = !EDGE || (i >= 0 && j >= 0 && i < nx && j < ny);
+    const bool in = !EDGE || interior(p, i, j), wall = grid && !in;
+    // the inward node of a wall node
+    const int ci = EDGE ? min(max(i, 1), nx - 2) : i, cj = EDGE ? min(max(j, 1), ny - 2) : j;
+    auto dist = [&](int x, int y) { return max(max(i0 - x, x - (i0 + kTile - 1)), max(j0 - y, y - (j0 + kTile - 1))); };
+    const bool near = grid && dist(ci, cj) <= 2;   // B, BH and their transposes
+    const bool own = grid && dist(i, j) <= 0;      // the tile proper
+    const int64_t pl = (int64_t)nx * ny;
+    const int gi = EDGE ? min(max(i, 0), nx - 1) : i, gj = EDGE ? min(max(j, 0), ny - 1) : j;
+    const int64_t id = at(p, gi, gj), rid = (int64_t)gj * p.pitch + gi;
+
+    double g[9], gadj[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) g[k] = (double)S::load(st, k * p.plane + rid, k);
+    const double lam_old = (double)lst[rid];
+    int64_t again = 0;   // an offset the compiler does not know, so that it loads the state again
+    asm volatile("" : "+s"(again));
+#pragma unroll
+    for (int k = 0; k < 9; ++k) gadj[k] = in ? fb_in[k * pl + id] : 0.0;   // wall f-hat+ is not used
+    const double lbar = lb_in[id];
+    const double aj = p.geo[gj], ajd = p.geo[ny + nx + gj];          // a_j, d a_j / d cot
+    const double si = p.geo[ny + gi], sid = p.geo[2 * ny + nx + gi];  // s_i, d s_i / d cot
+
+    const double acj = EDGE ? p.geo[cj] : aj, sci = EDGE ? p.geo[ny + ci] : si;
+    // s of the columns whose xi stencils read this node
+    double sc[5];
+#pragma unroll
+    for (int o = -2; o <= 2; ++o) sc[o + 2] = p.geo[ny + (EDGE ? min(max(i - o, 0), nx - 1) : i - o)];
+
+    // ------------------------------------------------------------- A
+    double lam, pw, m, Q, r, pxx, pyy, pxy, P, ux, uy;
+    bool floor;
+    moments(g, P, ux, uy);
+    const Equilibrium<double> eq(P, ux, uy);
+    {
+        double n[9];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) n[k] = eq.from(k, g[k]);
+        const double s58 = (n[5] + n[6]) + (n[7] + n[8]);
+        pxx = (n[1] + n[3]) + s58;
+        pyy = (n[2] + n[4]) + s58;
+        pxy = (n[5] - n[6]) + (n[7] - n[8]);
+        Q = pxx * pxx + 2.0 * pxy * pxy + pyy * pyy;
+        r = 1.0 / (2.0 * lam_old + p.dt);
+        const double gamma2 = 18.0 * Q * r * r;
+        floor = !(gamma2 > p.g2min);
+        m = floor ? p.g2min : gamma2;
+        pw = pow_pos<double>(m, p.expo);
+        lam = p.K3 * pw;
+        const double bb = 1.5 * p.dt / (2.0 * lam + p.dt);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) sh.bp[k][t] = g[k] - bb * n[k];
+    }
+    // CB^T: the adjoint of the interior values of the new state: its own plus what the wall nodes extrapolated from
+    // this node hand back
+    if (EDGE && in && (i == 1 || j == 1 || i == nx - 2 || j == ny - 2)) {
+        double x[9];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) x[k] = (double)S::load(st1, k * p.plane + rid, k);
+#pragma unroll 1
+        for (int q = 0; q < 3; ++q) {
+            int wi, wj;
+            if (!wall_of(p, i, j, q, wi, wj)) continue;
             double xb[9];
-            for (int k = 0; k < 9; ++k) xb[k] = fbar[k * pl + at(p, wi[q], wj[q])];
-            const double uwb = extrapolate_t(x, wj[q] == p.ny - 1 ? p.ulid : 0.0, xb, gb);
-            if (wj[q] == p.ny - 1) v[A_ULID] += uwb;
+#pragma unroll
+            for (int k = 0; k < 9; ++k) xb[k] = fb_in[k * pl + at(p, wi, wj)];
+            const double uwb = extrapolate_t(x, wj == ny - 1 ? p.ulid : 0.0, xb, gadj);
+            if (own && wj == ny - 1) v[A_ULID] += uwb;
         }
-        for (int k = 0; k < 9; ++k) G[k * pl + id] = gb[k];
-    } else if (node_of(p, i, j)) {
-        const int64_t id = at(p, i, j), pl = (int64_t)p.nx * p.ny;
-        for (int k = 0; k < 9; ++k) G[k * pl + id] = 0.0;   // wall f-hat+ is not used
     }
-    accumulate(p, S_CB, v);
-}
+#pragma unroll
+    for (int k = 1; k < 9; ++k) sh.G[k - 1][t] = gadj[k];
+    sh.X[0][t] = 0.0;   // read past the last plane of G by wall nodes three away from the tile, with zero weight
+    __syncthreads();
 
-// C^T: adjoint of f(t + dt/2) at every node (k = 0 carries no stream term)
-// and the cot / dt terms of Eq. (3.6) at interior nodes.
-__global__ __launch_bounds__(kB) void a_stage_c(AdjParams p, const double* G, const double* fh, double* fhb)
-{
-    double v[A_N] = {};
-    int i, j;
-    if (node_of(p, i, j)) {
-        const int64_t id = at(p, i, j), pl = (int64_t)p.nx * p.ny;
-        fhb[id] = 0.0;
-        for (int k = 1; k < 9; ++k) fhb[k * pl + id] = -p.dt * stencil_t(p, G + k * pl, i, j, k);
-        if (interior(p, i, j))
-            for (int k = 1; k < 9; ++k) {
-                const double gk = G[k * pl + id];
-                double mxi, meta;
-                stencil_parts(p, fh + k * pl, i, j, k, mxi, meta);
-                v[A_DT] -= gk * (c_xi(p, i, j, k) * mxi + (double)cyk(k) * meta);
-                v[A_COT] -= p.dt * gk * c_xi_dcot(p, i, j, k) * mxi;
+    // --------------------------------------------------------- B, BH
+    const int ct = t + (ci - i) + (cj - j) * kSide;   // the inward node in the tile
+    double x[9], hc = 0.0, den = 1.0;
+    double uxh = 0.0, uyh = 0.0, dh[9];   // velocity of the half-step input and e - x
+    if (near) {
+        x[0] = sh.bp[0][ct];
+#pragma unroll
+        for (int k = 1; k < 9; ++k) {
+            const double* plane = &sh.bp[k][ct];
+            const double c = acj * ((double)cxk(k) - (double)cyk(k) * sci);
+            double str = c * (mixed_at(plane, 1, c >= 0.0, EDGE && ci == (c >= 0.0 ? 1 : nx - 2), p.mix) * p.inv2dxi);
+            if (cyk(k) != 0)
+                str += (double)cyk(k) * (mixed_at(plane, kSide, cyk(k) > 0, EDGE && cj == (cyk(k) > 0 ? 1 : ny - 2), p.mix) * p.inv2deta);
+            x[k] = plane[0] - 0.5 * p.dt * str;
+            __builtin_amdgcn_sched_barrier(0);   // keeps the reads of later populations from being moved up
+        }
+        if (EDGE && wall) extrapolate(x, j == ny - 1 ? p.ulid : 0.0, x);
+        double Ph;
+        moments(x, Ph, uxh, uyh);
+        const Equilibrium<double> eh(Ph, uxh, uyh);
+        den = 4.0 * lam + p.dt;
+        hc = p.dt / den;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) dh[k] = eh.minus(k, x[k]);
+#pragma unroll
+        for (int k = 1; k < 9; ++k) sh.fh[k - 1][t] = x[k] + hc * dh[k];
+    }
+    __syncthreads();
+
+    // Transposed stencil of population k at this node: the sum over the interior nodes ix = i - o and jx = j - o whose
+    // stencils read it of their y times the weight they give to it.  The weights of all other nodes are zero; what is
+    // read for them is finite (the tile's row wraps, or plane 0 of X).
+    auto stencil_t = [&](const double* y, int k) {
+        double sx = 0.0;
+        if (!EDGE || (j >= 1 && j <= ny - 2)) {
+#pragma unroll
+            for (int o = -2; o <= 2; ++o) {
+                const int ix = i - o;
+                const double d = (double)cxk(k) - (double)cyk(k) * sc[o + 2];
+                double w = stencil_weight(o, d >= 0.0, EDGE && ix == 1, EDGE && ix == nx - 2, p.mix);
+                if (EDGE && (ix < 1 || ix > nx - 2)) w = 0.0;
+                sx += (y[-o] * d) * w;
             }
-    }
-    accumulate(p, S_C, v);
-}
+            sx *= aj * p.inv2dxi;
+        }
+        if (cyk(k) != 0 && (!EDGE || (i >= 1 && i <= nx - 2))) {
+            double se = 0.0;
+#pragma unroll
+            for (int o = -2; o <= 2; ++o) {
+                const int jx = j - o;
+                double w = stencil_weight(o, cyk(k) > 0, EDGE && jx == 1, EDGE && jx == ny - 2, p.mix);
+                if (EDGE && (jx < 1 || jx > ny - 2)) w = 0.0;
+                se += y[-o * kSide] * w;
+            }
+            sx += se * ((double)cyk(k) * p.inv2deta);
+        }
+        return sx;
+    };
+    // Adjoints of dt and cot through the stream term of one interior node: y_k is the adjoint of -scale dt S_k.
+    auto stream_adjoint = [&](const double (*tile)[kNodes], const double (&y)[9], double scale) {
+        double sdt = 0.0, scot = 0.0;
+#pragma unroll
+        for (int k = 1; k < 9; ++k) {
+            const double* plane = &tile[k - 1][t];
+            const double d = (double)cxk(k) - (double)cyk(k) * si, c = aj * d;
+            const double mxi = mixed_at(plane, 1, c >= 0.0, EDGE && i == (c >= 0.0 ? 1 : nx - 2), p.mix) * p.inv2dxi;
+            double str = c * mxi;
+            if (cyk(k) != 0)
+                str += (double)cyk(k) * (mixed_at(plane, kSide, cyk(k) > 0, EDGE && j == (cyk(k) > 0 ? 1 : ny - 2), p.mix) * p.inv2deta);
+            sdt += y[k] * str;
+            scot += y[k] * ((ajd * d - aj * (double)cyk(k) * sid) * mxi);
+            __builtin_amdgcn_sched_barrier(0);   // keeps the reads of later populations from being moved up
+        }
+        v[A_DT] -= scale * sdt;
+        v[A_COT] -= scale * p.dt * scot;
+    };
 
-// BH^T at every node: adjoint of the node's half-step input x (f-bar, or the
-// extrapolated wall value), written over fhb, and lambda-bar of this stage.
-__global__ __launch_bounds__(kB) void a_stage_bh(AdjParams p, const double* fb, const double* ln, double* fhb, double* lb)
-{
-    double v[A_N] = {};
-    int i, j;
-    if (node_of(p, i, j)) {
-        const int64_t id = at(p, i, j), pl = (int64_t)p.nx * p.ny;
-        double x[9], e[9], P, ux, uy;
-        half_input(p, fb, i, j, x);
-        moments(x, P, ux, uy);
-        equilibrium(P, ux, uy, e);
-        const double lam = ln[id], den = 4.0 * lam + p.dt, hc = p.dt / den;
-        double xb[9], eb[9], hcb = 0.0;
-        for (int k = 0; k < 9; ++k) {
-            const double y = fhb[k * pl + id];
+    // ----------------------------------------------------- C^T, BH^T
+    double xb[9], lb = 0.0;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) xb[k] = 0.0;
+    if (near) {
+        double eb[9], hcb = 0.0;
+        eb[0] = 0.0;   // population 0 is not streamed: its half-step adjoint is zero
+#pragma unroll
+        for (int k = 1; k < 9; ++k) {
+            const double y = -p.dt * stencil_t(&sh.G[k - 1][t], k);
             xb[k] = (1.0 - hc) * y;
             eb[k] = hc * y;
-            hcb += y * (e[k] - x[k]);
+            hcb += y * dh[k];
+            __builtin_amdgcn_sched_barrier(0);   // keeps the reads of later populations from being moved up
         }
-        double Pb = 0.0, uxb = 0.0, uyb = 0.0, gb[9];
-        equilibrium_t(ux, uy, eb, Pb, uxb, uyb);
-        moments_t(ux, uy, Pb, uxb, uyb, gb);
-        for (int k = 0; k < 9; ++k) fhb[k * pl + id] = xb[k] + gb[k];
-        lb[id] = hcb * (-4.0 * p.dt / (den * den));
-        v[A_DT] = hcb * (4.0 * lam / (den * den));
+        double Pb = 0.0, uxb = 0.0, uyb = 0.0, mb[9];
+        equilibrium_t(uxh, uyh, eb, Pb, uxb, uyb);
+        moments_t(uxh, uyh, Pb, uxb, uyb, mb);
+#pragma unroll
+        for (int k = 1; k < 9; ++k) xb[k] += mb[k];
+        lb = hcb * (-4.0 * p.dt / (den * den));
+        if (own) v[A_DT] += hcb * (4.0 * lam / (den * den));
     }
-    accumulate(p, S_BH, v);
-}
+    if (own && in) stream_adjoint(sh.fh, gadj, 1.0);
+#pragma unroll
+    for (int k = 1; k < 9; ++k) sh.X[k - 1][t] = xb[k];
+    __syncthreads();
 
-// Wall transpose of BH: adjoint of f-bar at interior nodes.
-__global__ __launch_bounds__(kB) void a_stage_bh2(AdjParams p, const double* fb, const double* xb, double* fbb)
-{
-    double v[A_N] = {};
-    int i, j;
-    if (node_of(p, i, j) && interior(p, i, j)) {
-        const int64_t id = at(p, i, j), pl = (int64_t)p.nx * p.ny;
-        double gb[9], x[9];
-        for (int k = 0; k < 9; ++k) {
-            gb[k] = xb[k * pl + id];
-            x[k] = fb[k * pl + id];
-        }
-        int wi[3], wj[3];
-        const int nw = walls_of(p, i, j, wi, wj);
-        for (int q = 0; q < nw; ++q) {
+    // wall transpose of BH: adjoint of f-bar at interior nodes, over G
+    if (EDGE && in && near && (i == 1 || j == 1 || i == nx - 2 || j == ny - 2)) {
+#pragma unroll 1
+        for (int q = 0; q < 3; ++q) {
+            int wi, wj;
+            if (!wall_of(p, i, j, q, wi, wj)) continue;
+            const int tw = t + (wi - i) + (wj - j) * kSide;
             double y[9];
-            for (int k = 0; k < 9; ++k) y[k] = xb[k * pl + at(p, wi[q], wj[q])];
-            const double uwb = extrapolate_t(x, wj[q] == p.ny - 1 ? p.ulid : 0.0, y, gb);
-            if (wj[q] == p.ny - 1) v[A_ULID] += uwb;
+            y[0] = 0.0;
+#pragma unroll
+            for (int k = 1; k < 9; ++k) y[k] = sh.X[k - 1][tw];
+            const double uwb = extrapolate_t(x, wj == ny - 1 ? p.ulid : 0.0, y, xb);
+            if (own && wj == ny - 1) v[A_ULID] += uwb;
         }
-        for (int k = 0; k < 9; ++k) fbb[k * pl + id] = gb[k];
     }
-    accumulate(p, S_BH2, v);
-}
+#pragma unroll
+    for (int k = 1; k < 9; ++k) sh.G[k - 1][t] = in ? xb[k] : 0.0;
+    __syncthreads();
 
-// B^T: adjoint of f-bar+ at every node, and the cot / dt terms of Eq. (3.7).
-__global__ __launch_bounds__(kB) void a_stage_b(AdjParams p, const double* fbb, const double* bp, double* bpb)
-{
-    double v[A_N] = {};
-    int i, j;
-    if (node_of(p, i, j)) {
-        const int64_t id = at(p, i, j), pl = (int64_t)p.nx * p.ny;
-        const bool in = interior(p, i, j);
-        bpb[id] = in ? fbb[id] : 0.0;
-        for (int k = 1; k < 9; ++k)
-            bpb[k * pl + id] = (in ? fbb[k * pl + id] : 0.0) - 0.5 * p.dt * stencil_t(p, fbb + k * pl, i, j, k);
-        if (in)
-            for (int k = 1; k < 9; ++k) {
-                const double yk = fbb[k * pl + id];
-                double mxi, meta;
-                stencil_parts(p, bp + k * pl, i, j, k, mxi, meta);
-                v[A_DT] -= 0.5 * yk * (c_xi(p, i, j, k) * mxi + (double)cyk(k) * meta);
-                v[A_COT] -= 0.5 * p.dt * yk * c_xi_dcot(p, i, j, k) * mxi;
-            }
-    }
-    accumulate(p, S_B, v);
-}
-
-// A^T at every node: from the adjoints of f-hat+ (G, zero on walls), f-bar+
-// (bpb) and lambda (lb from BH plus lbar, the adjoint of the stored Lambda of
-// t + dt) to the adjoint of the state at t, written over fbar / lbar.
-__global__ __launch_bounds__(kB) void a_stage_a(AdjParams p, const double* st, const double* G, const double* bpb,
-                                                const double* lb, double* fbar, double* lbar)
-{
-    double v[A_N] = {};
-    int i, j;
-    if (node_of(p, i, j)) {
-        const int64_t id = at(p, i, j), pl = (int64_t)p.nx * p.ny;
-        double g[9], e[9], P, ux, uy;
-        for (int k = 0; k < 9; ++k) g[k] = st[k * pl + id];
-        const double lam_old = st[9 * pl + id];
-        moments(g, P, ux, uy);
-        equilibrium(P, ux, uy, e);
-        double n[9];
-        for (int k = 0; k < 9; ++k) n[k] = g[k] - e[k];
-        const double s58 = (n[5] + n[6]) + (n[7] + n[8]);
-        const double pxx = (n[1] + n[3]) + s58, pyy = (n[2] + n[4]) + s58, pxy = (n[5] - n[6]) + (n[7] - n[8]);
-        const double Q = pxx * pxx + 2.0 * pxy * pxy + pyy * pyy;
-        const double r = 1.0 / (2.0 * lam_old + p.dt);
-        const double gamma2 = 18.0 * Q * r * r;
-        const bool floor = !(gamma2 > p.g2min);
-        const double m = floor ? p.g2min : gamma2;
-        const double pw = pow(m, p.expo), lam = p.K3 * pw;
+    // the stored state again: not held in registers since stage A
+#pragma unroll
+    for (int k = 0; k < 9; ++k) g[k] = (double)S::load(st, k * p.plane + rid + again, k);
+    // the weights of the transposed stencils are formed again in B^T: held from C^T on they would take 80 registers
+#pragma unroll
+    for (int o = 0; o < 5; ++o) asm volatile("" : "+v"(sc[o]));
+    // ------------------------------------------------------ B^T, A^T
+    if (own) {
+        double yb[9];
+        yb[0] = 0.0;
+#pragma unroll
+        for (int k = 1; k < 9; ++k) {
+            yb[k] = (in ? xb[k] : 0.0) - 0.5 * p.dt * stencil_t(&sh.G[k - 1][t], k);
+            __builtin_amdgcn_sched_barrier(0);   // keeps the reads of later populations from being moved up
+        }
+        if (in) stream_adjoint(sh.bp + 1, xb, 0.5);
         const double R = 1.0 / (2.0 * lam + p.dt), bh = 2.0 * p.dt * R, bb = 1.5 * p.dt * R;
         // f-hat+ = g + bh (e - g), f-bar+ = g + bb (e - g)
         double gb[9], eb[9], bhb = 0.0, bbb = 0.0;
+#pragma unroll
         for (int k = 0; k < 9; ++k) {
-            const double yh = G[k * pl + id], yb = bpb[k * pl + id];
-            gb[k] = (1.0 - bh) * yh + (1.0 - bb) * yb;
-            eb[k] = bh * yh + bb * yb;
-            bhb += yh * (e[k] - g[k]);
-            bbb += yb * (e[k] - g[k]);
+            const double yh = gadj[k];
+            gb[k] = (1.0 - bh) * yh + (1.0 - bb) * yb[k];
+            eb[k] = bh * yh + bb * yb[k];
+            const double d = eq.minus(k, g[k]);
+            bhb += yh * d;
+            bbb += yb[k] * d;
         }
         const double Rb = 2.0 * p.dt * bhb + 1.5 * p.dt * bbb;
         v[A_DT] += 2.0 * R * bhb + 1.5 * R * bbb - Rb * R * R;
-        const double lamb = lb[id] + lbar[id] - 2.0 * Rb * R * R;
+        const double lamb = lb + lbar - 2.0 * Rb * R * R;
         // lambda = K3 m^expo
         v[A_K3] = lamb * pw;
         v[A_EXPO] = lamb * lam * log(m);
@@ -512,6 +530,7 @@ __global__ __launch_bounds__(kB) void a_stage_a(AdjParams p, const double* st, c
             lam_old_b = -2.0 * rb * r * r;
             v[A_DT] -= rb * r * r;
             const double pxxb = 2.0 * pxx * Qb, pyyb = 2.0 * pyy * Qb, pxyb = 4.0 * pxy * Qb;
+#pragma unroll
             for (int k = 1; k < 9; ++k) {
                 const double cx = cxk(k), cy = cyk(k);
                 const double nb = cx * cx * pxxb + cx * cy * pxyb + cy * cy * pyyb;
@@ -522,10 +541,27 @@ __global__ __launch_bounds__(kB) void a_stage_a(AdjParams p, const double* st, c
         double Pb = 0.0, uxb = 0.0, uyb = 0.0, mb[9];
         equilibrium_t(ux, uy, eb, Pb, uxb, uyb);
         moments_t(ux, uy, Pb, uxb, uyb, mb);
-        for (int k = 0; k < 9; ++k) fbar[k * pl + id] = gb[k] + mb[k];
-        lbar[id] = lam_old_b;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) fb_out[k * pl + id] = gb[k] + mb[k];
+        lb_out[id] = lam_old_b;
     }
-    accumulate(p, S_A, v);
+    // sums over the tile: each wavefront, then the wavefronts, in a fixed order
+    __shared__ double sums[kThreads / kWaveLanes][A_N];
+#pragma unroll
+    for (int q = 0; q < A_N; ++q) {
+        if (q == A_LAM0) continue;   // none in a step
+        double sv = v[q];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) sv += __shfl_xor(sv, off, kWaveLanes);
+        if (threadIdx.x % kWaveLanes == 0) sums[threadIdx.x / kWaveLanes][q] = sv;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < A_N && threadIdx.x != A_LAM0) {
+        double sv = 0.0;
+#pragma unroll
+        for (int w = 0; w < kThreads / kWaveLanes; ++w) sv += sums[w][t];
+        p.acc[((int64_t)S_STEP * p.blocks + by * fr.tx + bx) * A_N + t] += sv;
+    }
 }
 
 // Step (1)^T: f-hat = e(0, u) with u = (U, 0) on the lid row, Lambda = lam0.
@@ -554,27 +590,50 @@ struct AdjointSweep::Impl {
     AdjParams p{};
     double cot = 0.0;
     size_t nn = 0, nb = 0;
+    int prec = 0, cur = 0;
+    TileFrame frame{};
     double *geo = nullptr, *acc = nullptr, *jpart = nullptr;
-    double *bp = nullptr, *fb = nullptr, *fh = nullptr, *ln = nullptr;
-    double *fbar = nullptr, *lbar = nullptr, *G = nullptr, *w1 = nullptr, *lb = nullptr, *fbb = nullptr;
+    double *fbar[2] = {nullptr, nullptr}, *lbar[2] = {nullptr, nullptr};   // adjoint of the state, before and after a step
 };
 
 AdjointSweep::AdjointSweep() : d(new Impl) {}
 
-AdjointSweep::~AdjointSweep()
+AdjointSweep::~AdjointSweep() { delete d; }
+
+namespace {
+
+struct SweepSizes {
+    size_t nn, nb, tx, ty, slots;   // slots: accumulators of one kind
+    explicit SweepSizes(const CavityDesc& c)
+        : nn((size_t)c.nx * c.ny), nb((nn + kB - 1) / kB), tx((size_t)(c.nx + kTile - 1) / kTile),
+          ty((size_t)(c.ny + kTile - 1) / kTile), slots(tx * ty > nb ? tx * ty : nb)
+    {
+    }
+};
+
+}  // namespace
+
+// doubles: metric tables, accumulators, objective partial sums, two adjoint states
+size_t AdjointSweep::work_doubles(const CavityDesc& c)
 {
-    double* ptrs[] = {d->geo, d->acc, d->jpart, d->bp, d->fb, d->fh, d->ln, d->fbar, d->lbar, d->G, d->w1, d->lb, d->fbb};
-    for (double* q : ptrs)
-        if (q) (void)hipFree(q);
-    delete d;
+    const SweepSizes z(c);
+    return 2 * (size_t)(c.nx + c.ny) + S_N * z.slots * A_N + z.nb + 20 * z.nn;
 }
 
-hipError_t AdjointSweep::init(const CavityDesc& c, hipStream_t s)
+hipError_t AdjointSweep::init(const CavityDesc& c, int prec, double* work, hipStream_t s)
 {
     Impl& m = *d;
+    const SweepSizes z(c);
     m.cot = c.cot;
-    m.nn = (size_t)c.nx * c.ny;
-    m.nb = (m.nn + kB - 1) / kB;
+    m.nn = z.nn;
+    m.nb = z.nb;
+    m.prec = prec;
+    // a tile and its halo are clear of the walls' neighbours: T b - 4 >= 2 and T (b + 1) + 4 <= n - 2
+    auto inner_end = [](int n, int lo) { return n >= 2 * kTile + 6 ? (n - 6) / kTile : lo; };
+    TileFrame& fr = m.frame;
+    fr = {(int)z.tx, (int)z.ty, 1, inner_end(c.nx, 1), 1, inner_end(c.ny, 1)};
+    // while every tile has a CU of its own, one launch of the general kernel is the shorter
+    if (fr.tx * fr.ty <= 256 || fr.xb <= fr.xa || fr.yb <= fr.ya) fr.xa = fr.xb = fr.ya = fr.yb = 0;
     std::vector<double> geo(2 * (c.nx + c.ny));
     for (int j = 0; j < c.ny; ++j) {
         const double eta = j * c.deta, a = 1.0 / (1.0 + 2.0 * c.cot * eta);
@@ -586,24 +645,26 @@ hipError_t AdjointSweep::init(const CavityDesc& c, hipStream_t s)
         geo[c.ny + i] = c.cot * w;
         geo[2 * c.ny + c.nx + i] = w;
     }
-    struct {
-        double** ptr;
-        size_t n;
-    } bufs[] = {{&m.geo, geo.size()}, {&m.acc, (size_t)S_N * m.nb * A_N}, {&m.jpart, m.nb}, {&m.bp, 9 * m.nn},
-                {&m.fb, 9 * m.nn}, {&m.fh, 9 * m.nn}, {&m.ln, m.nn}, {&m.fbar, 9 * m.nn}, {&m.lbar, m.nn},
-                {&m.G, 9 * m.nn}, {&m.w1, 9 * m.nn}, {&m.lb, m.nn}, {&m.fbb, 9 * m.nn}};
-    for (auto& b : bufs) {
-        hipError_t e = hipMalloc(reinterpret_cast<void**>(b.ptr), b.n * sizeof(double));
-        if (e != hipSuccess) return e;
+    auto take = [&](size_t n) {
+        double* q = work;
+        work += n;
+        return q;
+    };
+    m.geo = take(geo.size());
+    m.acc = take(S_N * z.slots * A_N);
+    m.jpart = take(z.nb);
+    for (int b = 0; b < 2; ++b) {
+        m.fbar[b] = take(9 * z.nn);
+        m.lbar[b] = take(z.nn);
     }
     hipError_t e = hipMemcpyAsync(m.geo, geo.data(), geo.size() * sizeof(double), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemsetAsync(m.acc, 0, (size_t)S_N * m.nb * A_N * sizeof(double), s);
-    // a_stage_b reads f-bar only at interior nodes; clear the walls once
-    if (e == hipSuccess) e = hipMemsetAsync(m.fb, 0, 9 * m.nn * sizeof(double), s);
-    if (e == hipSuccess) e = hipMemsetAsync(m.fbb, 0, 9 * m.nn * sizeof(double), s);
+    if (e == hipSuccess) e = hipMemsetAsync(m.acc, 0, S_N * z.slots * A_N * sizeof(double), s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);   // geo lives on the host's stack
     AdjParams& p = m.p;
     p.nx = c.nx;
     p.ny = c.ny;
+    p.pitch = c.pitch;
+    p.plane = c.plane;
     p.dt = c.dt;
     p.K3 = 3.0 * c.K;
     p.expo = c.expo;
@@ -616,30 +677,39 @@ hipError_t AdjointSweep::init(const CavityDesc& c, hipStream_t s)
     p.deta = c.deta;
     p.geo = m.geo;
     p.acc = m.acc;
-    p.blocks = (int)m.nb;
+    p.blocks = (int)z.slots;
     return e;
 }
 
 hipError_t AdjointSweep::objective(const double* state, hipStream_t s)
 {
     Impl& m = *d;
-    hipLaunchKernelGGL(a_objective, dim3(m.nb), dim3(kB), 0, s, m.p, m.cot, state, m.fbar, m.lbar, m.jpart);
+    hipLaunchKernelGGL(a_objective, dim3(m.nb), dim3(kB), 0, s, m.p, m.cot, state, m.fbar[m.cur], m.lbar[m.cur], m.jpart);
     return hipGetLastError();
 }
 
-hipError_t AdjointSweep::step_back(const double* st, const double* st1, hipStream_t s)
+hipError_t AdjointSweep::step_back(const void* f, const void* l, const void* f1, hipStream_t s)
 {
     Impl& m = *d;
-    const dim3 g(m.nb), b(kB);
-    hipLaunchKernelGGL(r_stage_a, g, b, 0, s, m.p, st, m.bp, m.ln);
-    hipLaunchKernelGGL(r_stage_b, g, b, 0, s, m.p, m.bp, m.fb);
-    hipLaunchKernelGGL(r_stage_bh, g, b, 0, s, m.p, m.fb, m.ln, m.fh);
-    hipLaunchKernelGGL(a_stage_cb, g, b, 0, s, m.p, st1, m.fbar, m.G);
-    hipLaunchKernelGGL(a_stage_c, g, b, 0, s, m.p, m.G, m.fh, m.w1);
-    hipLaunchKernelGGL(a_stage_bh, g, b, 0, s, m.p, m.fb, m.ln, m.w1, m.lb);
-    hipLaunchKernelGGL(a_stage_bh2, g, b, 0, s, m.p, m.fb, m.w1, m.fbb);
-    hipLaunchKernelGGL(a_stage_b, g, b, 0, s, m.p, m.fbb, m.bp, m.w1);
-    hipLaunchKernelGGL(a_stage_a, g, b, 0, s, m.p, st, m.G, m.w1, m.lb, m.fbar, m.lbar);
+    auto go = [&](auto prec) {
+        constexpr int P = decltype(prec)::value;
+        using F = typename Storage<P>::F;
+        auto launch = [&](auto kernel, int tiles) {
+            hipLaunchKernelGGL(kernel, dim3(tiles), dim3(kThreads), 0, s, m.p, m.frame, static_cast<const F*>(f),
+                               static_cast<const typename Storage<P>::L*>(l), static_cast<const F*>(f1), m.fbar[m.cur],
+                               m.lbar[m.cur], m.fbar[m.cur ^ 1], m.lbar[m.cur ^ 1]);
+        };
+        const int edge = m.frame.edge_tiles(), inner = m.frame.tx * m.frame.ty - edge;
+        if (inner > 0) launch(k_adjoint_step<P, false>, inner);
+        launch(k_adjoint_step<P, true>, edge);
+    };
+    // the FP32 modes store alike
+    switch (m.prec) {
+    case P_FP64: go(std::integral_constant<int, P_FP64>{}); break;
+    case P_FP16DEV: go(std::integral_constant<int, P_FP16DEV>{}); break;
+    default: go(std::integral_constant<int, P_FP32>{}); break;
+    }
+    m.cur ^= 1;
     return hipGetLastError();
 }
 
@@ -647,15 +717,15 @@ hipError_t AdjointSweep::finish(const CavityDesc& c, double dt_dcot, double lam0
                                 hipStream_t s, double* J, double grad[3])
 {
     Impl& m = *d;
-    hipLaunchKernelGGL(a_initial, dim3(m.nb), dim3(kB), 0, s, m.p, m.fbar, m.lbar);
+    hipLaunchKernelGGL(a_initial, dim3(m.nb), dim3(kB), 0, s, m.p, m.fbar[m.cur], m.lbar[m.cur]);
     hipError_t e = hipGetLastError();
-    std::vector<double> acc((size_t)S_N * m.nb * A_N), jp(m.nb);
+    std::vector<double> acc((size_t)S_N * m.p.blocks * A_N), jp(m.nb);
     if (e == hipSuccess) e = hipMemcpyAsync(acc.data(), m.acc, acc.size() * sizeof(double), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipMemcpyAsync(jp.data(), m.jpart, jp.size() * sizeof(double), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
     double t[A_N] = {};
-    for (size_t q = 0; q < (size_t)S_N * m.nb; ++q)
+    for (size_t q = 0; q < (size_t)S_N * m.p.blocks; ++q)
         for (int a = 0; a < A_N; ++a) t[a] += acc[q * A_N + a];
     double j = 0.0;
     for (double x : jp) j += x;

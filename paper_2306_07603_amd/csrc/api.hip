@@ -369,11 +369,10 @@ hipError_t launch_items(int shape, int prec, bool impl, const StepArgs& a, const
                            : launch_tile_step(shape, prec, impl, a, items, w0, nw, residual, s);
 }
 
-// Enqueue one time step of the running cavities, reading buffer `cur`;
-// `local` numbers the step within its call or graph (stochastic rounding).
-int enqueue_step(ifdlbm_s* h, bool residual, uint32_t local)
+// Enqueue one time step of the running cavities with the buffers of `a`; `local` numbers the step within its call
+// or graph (stochastic rounding).
+int enqueue_step(ifdlbm_s* h, bool residual, uint32_t local, StepArgs a)
 {
-    StepArgs a = step_args(h);
     a.step = local;
     const int prec = h->opt.precision;
     const bool staged = h->opt.kernel == IFDLBM_KERNEL_STAGED;
@@ -397,6 +396,9 @@ int enqueue_step(ifdlbm_s* h, bool residual, uint32_t local)
     if (e != hipSuccess) return fail(IFDLBM_EDEVICE, std::string("step launch: ") + hipGetErrorString(e));
     return IFDLBM_OK;
 }
+
+// The same from buffer `cur` to the other.
+int enqueue_step(ifdlbm_s* h, bool residual, uint32_t local) { return enqueue_step(h, residual, local, step_args(h)); }
 
 // Probe record of the current state (after a step).
 int enqueue_probe(ifdlbm_s* h)
@@ -1138,62 +1140,74 @@ static int ifdlbm_adjoint_impl(const ifdlbm_cavity* cav, const ifdlbm_options* o
     if (rc) return rc;
     const CavityDesc c = h->desc[0];
     const int prec = h->opt.precision;
-    const size_t nn = (size_t)c.nx * c.ny, sd = 10 * nn;   // doubles per FP64 state
+    const size_t nn = (size_t)c.nx * c.ny;
     const int64_t seg = std::min<int64_t>(checkpoint_every, n_steps);
-    const int64_t n_ck = (n_steps + seg - 1) / seg;
+    const int64_t n_ck = (n_steps + seg - 1) / seg;   // segments; the last one needs no checkpoint
+    auto up = [](size_t n) { return (n + 255) / 256 * 256; };
     const size_t fbytes = h->f_elems * f_elem_size(prec), lbytes = h->l_elems * l_elem_size(prec);
-    char *ck_f = nullptr, *ck_l = nullptr;
-    uint32_t* ck_seed = nullptr;
-    double* traj = nullptr;
-    std::vector<int> ck_cur(n_ck);
-    std::vector<int64_t> ck_count(n_ck);
+    const size_t fslot = up(fbytes), slot = fslot + up(lbytes), sbytes = up(sizeof(uint32_t) * n_ck);
+    // one allocation: a raw state per checkpoint and per step of a segment, the random-word counters, the sweep's work
+    char* mem = nullptr;
     AdjointSweep sweep;
     hipStream_t s = h->stream;
-    if (!rc) rc = dalloc(&ck_f, fbytes * n_ck);
-    if (!rc) rc = dalloc(&ck_l, lbytes * n_ck);
-    if (!rc) rc = dalloc(&ck_seed, sizeof(uint32_t) * n_ck);
-    if (!rc) rc = dalloc(&traj, sizeof(double) * sd * (seg + 1));
+    if (!rc) rc = dalloc(&mem, slot * (n_ck - 1 + seg + 1) + sbytes + AdjointSweep::work_doubles(c) * sizeof(double));
+    char* const traj = mem + slot * (n_ck - 1);
+    char* const ck_seed = traj + slot * (seg + 1);
     if (!rc) {
-        hipError_t e = sweep.init(c, s);
-        if (e != hipSuccess) rc = fail(e == hipErrorOutOfMemory ? IFDLBM_ENOMEM : IFDLBM_EDEVICE,
-                                       std::string("adjoint buffers: ") + hipGetErrorString(e));
+        hipError_t e = sweep.init(c, prec, reinterpret_cast<double*>(ck_seed + sbytes), s);
+        if (e != hipSuccess) rc = fail(IFDLBM_EDEVICE, std::string("adjoint buffers: ") + hipGetErrorString(e));
     }
     auto hip_ok = [&](hipError_t e, const char* what) {
         if (e == hipSuccess) return true;
         rc = fail(IFDLBM_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
         return false;
     };
-    auto to_traj = [&](int64_t slot) {
-        return hip_ok(launch_state_out(prec, h->d_f[h->cur], h->d_l[h->cur], c, 0.0, traj + slot * sd,
-                                       traj + slot * sd + 9 * nn, s), "state out");
+    auto copy = [&](void* dst, const void* src, size_t bytes, const char* what) {
+        return hip_ok(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, s), what);
     };
-    // forward sweep, keeping the state at every checkpoint
-    for (int64_t q = 0; q < n_ck && !rc; ++q) {
-        ck_cur[q] = h->cur;
-        ck_count[q] = h->step_count;
-        if (!hip_ok(hipMemcpyAsync(ck_f + q * fbytes, h->d_f[h->cur], fbytes, hipMemcpyDeviceToDevice, s), "checkpoint") ||
-            !hip_ok(hipMemcpyAsync(ck_l + q * lbytes, h->d_l[h->cur], lbytes, hipMemcpyDeviceToDevice, s), "checkpoint") ||
-            !hip_ok(hipMemcpyAsync(ck_seed + q, h->d_seed, sizeof(uint32_t), hipMemcpyDeviceToDevice, s), "checkpoint"))
+    auto save = [&](char* to) {   // the handle's state into a raw state
+        return copy(to, h->d_f[h->cur], fbytes, "checkpoint") && copy(to + fslot, h->d_l[h->cur], lbytes, "checkpoint");
+    };
+    // One step from a raw state to the next.  Every step draws the random words of a call of its own, so that a
+    // segment recomputed with its counter restored stores the same bits.
+    const bool draws = prec == P_FP32SR || prec == P_FP32SRF || prec == P_FP16DEV;
+    auto step = [&](const char* from, char* to) {
+        if (draws && !hip_ok(launch_seed_bump(h->d_seed, s), "seed")) return;
+        StepArgs a = step_args(h);
+        a.f_in = from;
+        a.l_in = from + fslot;
+        a.f_out = to;
+        a.l_out = to + fslot;
+        rc = enqueue_step(h, false, 0, a);
+    };
+    // forward sweep up to the last segment, keeping the state at every checkpoint
+    for (int64_t q = 0; q < n_ck - 1 && !rc; ++q) {
+        if (!save(mem + q * slot) ||
+            !copy(ck_seed + q * sizeof(uint32_t), h->d_seed, sizeof(uint32_t), "checkpoint"))
             break;
-        const int64_t steps = std::min(seg, n_steps - q * seg);
-        for (int64_t t = 0; t < steps && !rc; ++t) rc = eager_steps(h, 1);
+        for (int64_t t = 0; t < seg && !rc; ++t) rc = eager_steps(h, 1);
     }
-    // reverse sweep: recompute each segment from its checkpoint, then walk it backwards
+    // reverse sweep: the states of each segment from its first one, then walk it backwards
     for (int64_t q = n_ck - 1; q >= 0 && !rc; --q) {
-        h->cur = ck_cur[q];
-        h->step_count = ck_count[q];
-        if (!hip_ok(hipMemcpyAsync(h->d_f[h->cur], ck_f + q * fbytes, fbytes, hipMemcpyDeviceToDevice, s), "restore") ||
-            !hip_ok(hipMemcpyAsync(h->d_l[h->cur], ck_l + q * lbytes, lbytes, hipMemcpyDeviceToDevice, s), "restore") ||
-            !hip_ok(hipMemcpyAsync(h->d_seed, ck_seed + q, sizeof(uint32_t), hipMemcpyDeviceToDevice, s), "restore") ||
-            !to_traj(0))
-            break;
         const int64_t steps = std::min(seg, n_steps - q * seg);
-        for (int64_t t = 1; t <= steps && !rc; ++t)
-            if (!(rc = eager_steps(h, 1))) to_traj(t);
+        if (q == n_ck - 1) {
+            if (!save(traj)) break;
+        } else if (!copy(traj, mem + q * slot, slot, "restore") ||
+                   !copy(h->d_seed, ck_seed + q * sizeof(uint32_t), sizeof(uint32_t), "restore")) {
+            break;
+        }
+        for (int64_t t = 0; t < steps && !rc; ++t) step(traj + t * slot, traj + (t + 1) * slot);
         if (rc) break;
-        if (q == n_ck - 1 && !hip_ok(sweep.objective(traj + steps * sd, s), "objective")) break;
-        for (int64_t t = steps - 1; t >= 0 && !rc; --t)
-            hip_ok(sweep.step_back(traj + t * sd, traj + (t + 1) * sd, s), "adjoint step");
+        if (q == n_ck - 1) {
+            const char* last = traj + steps * slot;
+            if (!hip_ok(launch_state_out(prec, last, last + fslot, c, 0.0, h->d_scratch, h->d_scratch + 9 * nn, s), "state out") ||
+                !hip_ok(sweep.objective(h->d_scratch, s), "objective"))
+                break;
+        }
+        for (int64_t t = steps - 1; t >= 0 && !rc; --t) {
+            const char *at = traj + t * slot, *next = at + slot;
+            hip_ok(sweep.step_back(at, at + fslot, next, s), "adjoint step");
+        }
         if (!rc && !hip_ok(hipStreamSynchronize(s), "adjoint segment")) break;
     }
     if (!rc) {
@@ -1209,8 +1223,7 @@ static int ifdlbm_adjoint_impl(const ifdlbm_cavity* cav, const ifdlbm_options* o
             rc = fail(IFDLBM_EDIVERGED, "the trajectory or its adjoint became non-finite");
     }
     (void)hipStreamSynchronize(s);
-    for (void* p : {static_cast<void*>(ck_f), static_cast<void*>(ck_l), static_cast<void*>(ck_seed), static_cast<void*>(traj)})
-        if (p) (void)hipFree(p);
+    if (mem) (void)hipFree(mem);
     ifdlbm_destroy(h);
     return rc;
 }
