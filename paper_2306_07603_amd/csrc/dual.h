@@ -1,6 +1,5 @@
 // dual.h -- forward-mode (tangent-linear) arithmetic: a value and its
-// derivatives with respect to N parameters, carried through every operation
-// of the per-node IFDLBM arithmetic templates.
+// derivatives with respect to N parameters.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -53,35 +52,6 @@ template <int N> __host__ __device__ inline Dual<N> operator*(const Dual<N>& a, 
     for (int i = 0; i < N; ++i) r.d[i] = a.d[i] * b.v + a.v * b.d[i];
     return r;
 }
-template <int N> __host__ __device__ inline Dual<N> operator/(const Dual<N>& a, const Dual<N>& b)
-{
-    const double q = a.v / b.v;
-    Dual<N> r(q);
-    for (int i = 0; i < N; ++i) r.d[i] = (a.d[i] - q * b.d[i]) / b.v;
-    return r;
-}
 template <int N> __host__ __device__ inline Dual<N>& operator+=(Dual<N>& a, const Dual<N>& b) { return a = a + b; }
-template <int N> __host__ __device__ inline Dual<N>& operator-=(Dual<N>& a, const Dual<N>& b) { return a = a - b; }
-template <int N> __host__ __device__ inline Dual<N>& operator*=(Dual<N>& a, const Dual<N>& b) { return a = a * b; }
-template <int N> __host__ __device__ inline bool operator>(const Dual<N>& a, const Dual<N>& b) { return a.v > b.v; }
-template <int N> __host__ __device__ inline bool operator<(const Dual<N>& a, const Dual<N>& b) { return a.v < b.v; }
-template <int N> __host__ __device__ inline bool operator>=(const Dual<N>& a, const Dual<N>& b) { return a.v >= b.v; }
-template <int N> __host__ __device__ inline bool operator!=(const Dual<N>& a, const Dual<N>& b) { return a.v != b.v; }
-
-// x^y for x > 0: d(x^y) = x^y (y dx / x + ln x dy)
-template <int N> __host__ __device__ inline Dual<N> dual_pow(const Dual<N>& x, const Dual<N>& y)
-{
-    const double p = pow(x.v, y.v), lx = log(x.v);
-    Dual<N> r(p);
-    for (int i = 0; i < N; ++i) r.d[i] = p * (y.v * x.d[i] / x.v + lx * y.d[i]);
-    return r;
-}
-
-template <int N> __device__ inline bool dual_isfinite(const Dual<N>& x)
-{
-    bool ok = isfinite(x.v);
-    for (int i = 0; i < N; ++i) ok = ok && isfinite(x.d[i]);
-    return ok;
-}
 
 }  // namespace ifd

@@ -2,7 +2,7 @@
 // angle theta (radians), the power-law index n and the lid speed U, by
 // forward (tangent-linear) differentiation of the discrete IFDLBM step.
 //
-// Every quantity of the staged step carries its value and its three partial
+// Every quantity of the step carries its value and its three partial
 // derivatives (Dual<3>, FP64).  The parameters enter through the metric terms
 // a_j = 1/(1 + 2 eta_j cot theta), s_i = cot theta (2 xi_i - 1) (Eqs. 3.2-3.8.2),
 // the time step (CFL rule on the contravariant speed 1 + cot theta), the
@@ -24,63 +24,296 @@ namespace ifd {
 
 using D3 = Dual<3>;
 
-template <> __device__ __forceinline__ D3 recip<D3>(D3 x) { return D3(1.0) / x; }
-template <> __host__ __device__ __forceinline__ D3 pow_pos<D3>(D3 x, D3 y) { return dual_pow(x, y); }
-
 namespace {
+
+// A quantity that depends on theta only (metric terms, time step): value and theta derivative.
+struct Th {
+    double v, d;
+};
 
 struct TParams {
     int nx, ny;
-    D3 dt, K, expo, g2min, mix, ulid, inv2dxi, inv2deta, cot, lam0;
+    double mix, g2min, inv2dxi, inv2deta;
+    Th dt, cot;
+    D3 K, expo, ulid, lam0;
     double dxi, deta;
 };
 
-// Step (2), Eqs. (2.12)-(2.14) and (1.4), as relaxation_time but with every
-// parameter differentiated (no Newtonian shortcut: d mu / d n != 0 at n = 1).
-__device__ D3 relax_t(const D3 g[9], const D3 e[9], D3 lam_old, const TParams& c)
+// ------------------------------------------------ arithmetic of the step
+// Written out for what is a constant (four products), what depends on theta
+// only (five) and what carries all three derivatives (seven).
+
+__device__ __forceinline__ D3 times(double a, const D3& x)
 {
-    D3 n[9];
-    for (int k = 0; k < 9; ++k) n[k] = g[k] - e[k];
-    const D3 s58 = (n[5] + n[6]) + (n[7] + n[8]);
-    const D3 pxx = (n[1] + n[3]) + s58;
-    const D3 pyy = (n[2] + n[4]) + s58;
-    const D3 pxy = (n[5] - n[6]) + (n[7] - n[8]);
-    const D3 r = D3(1.0) / (D3(2.0) * lam_old + c.dt);
-    D3 gamma2 = D3(18.0) * (pxx * pxx + D3(2.0) * pxy * pxy + pyy * pyy) * r * r;
-    if (!(gamma2 > c.g2min)) gamma2 = c.g2min;
-    return D3(3.0) * c.K * dual_pow(gamma2, c.expo);
+    D3 r;
+    r.v = a * x.v;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) r.d[q] = a * x.d[q];
+    return r;
 }
 
-__device__ D3 transport_t(const D3* plane, const TParams& c, const D3* geo, int i, int j, int k)
+__device__ __forceinline__ D3 axpy(double a, const D3& x, const D3& y)   // a x + y
 {
-    const int cx = cxk(k), cy = cyk(k);
-    D3 term(0.0);
-    // the xi term is kept where c_xi is zero: its theta derivative need not be
-    // (the upwind side is then the c >= 0 one, as in the forward step)
-    const D3 cxi = geo[j] * (D3((double)cx) - D3((double)cy) * geo[c.ny + i]);
+    D3 r;
+    r.v = __builtin_fma(a, x.v, y.v);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) r.d[q] = __builtin_fma(a, x.d[q], y.d[q]);
+    return r;
+}
+
+__device__ __forceinline__ D3 muladd(const D3& a, const D3& b, const D3& c)   // a b + c
+{
+    D3 r;
+    r.v = __builtin_fma(a.v, b.v, c.v);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) r.d[q] = __builtin_fma(a.d[q], b.v, __builtin_fma(a.v, b.d[q], c.d[q]));
+    return r;
+}
+
+__device__ __forceinline__ D3 muladd(const Th& a, const D3& b, const D3& c)   // a b + c
+{
+    D3 r;
+    r.v = __builtin_fma(a.v, b.v, c.v);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) r.d[q] = __builtin_fma(a.v, b.d[q], c.d[q]);
+    r.d[0] = __builtin_fma(a.d, b.v, r.d[0]);
+    return r;
+}
+
+// Eqs. (2.10)-(2.11) on deviations (see moments in lbm_device.h)
+__device__ __forceinline__ void moments_t(const D3 (&g)[9], D3& P, D3& ux, D3& uy)
+{
+    ux = (g[1] - g[3]) + (g[5] - g[6]) - (g[7] - g[8]);
+    uy = (g[2] - g[4]) + (g[5] + g[6]) - (g[7] + g[8]);
+    const D3 s = ((g[1] + g[2]) + (g[3] + g[4])) + ((g[5] + g[6]) + (g[7] + g[8]));
+    P.v = 0.6 * s.v - 0.4 * (ux.v * ux.v + uy.v * uy.v);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) P.d[q] = 0.6 * s.d[q] - 0.8 * (ux.v * ux.d[q] + uy.v * uy.d[q]);
+}
+
+// Eq. (2.8) (see Equilibrium in lbm_device.h)
+struct EquilibriumT {
+    D3 base, e0, ux, uy;
+    __device__ __forceinline__ EquilibriumT(const D3& P, const D3& x, const D3& y) : ux(x), uy(y)
     {
-        const D3* row = plane + (int64_t)j * c.nx;
-        const bool pos = cxi.v >= 0.0;
-        const D3 m2 = (pos && i >= 2) ? row[i - 2] : D3(0.0);
-        const D3 p2 = (!pos && i <= c.nx - 3) ? row[i + 2] : D3(0.0);
-        term += cxi * (mixed_diff_2h(m2, row[i - 1], row[i], row[i + 1], p2, pos, i == 1, i == c.nx - 2, c.mix) * c.inv2dxi);
+        D3 uu;
+        uu.v = x.v * x.v + y.v * y.v;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) uu.d[q] = 2.0 * (x.v * x.d[q] + y.v * y.d[q]);
+        base = axpy(-1.5, uu, times(3.0, P));
+        e0 = axpy(-5.0 / 3.0, P, times(-2.0 / 3.0, uu));
     }
-    if (cy != 0) {
-        const D3* col = plane + i;
-        const int p = c.nx;
-        const bool pos = cy > 0;
-        const D3 m2 = (pos && j >= 2) ? col[(j - 2) * p] : D3(0.0);
-        const D3 p2 = (!pos && j <= c.ny - 3) ? col[(j + 2) * p] : D3(0.0);
-        term += D3((double)cy) * (mixed_diff_2h(m2, col[(j - 1) * p], col[j * p], col[(j + 1) * p], p2, pos, j == 1,
-                                                j == c.ny - 2, c.mix) * c.inv2deta);
+    // e_k + s v for s = 1 or -1
+    __device__ __forceinline__ D3 plus(int k, double s, const D3& v) const
+    {
+        if (k == 0) return axpy(s, v, e0);
+        const D3 cu = k == 1 ? ux : k == 2 ? uy : k == 3 ? -ux : k == 4 ? -uy : k == 5 ? ux + uy : k == 6 ? uy - ux : k == 7 ? -(ux + uy) : ux - uy;
+        const double w = k < 5 ? 1.0 / 9.0 : 1.0 / 36.0, slope = 3.0 + 9.0 * cu.v;
+        D3 r;
+        r.v = __builtin_fma(w, __builtin_fma(cu.v, __builtin_fma(4.5, cu.v, 3.0), base.v), s * v.v);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) r.d[q] = __builtin_fma(w, __builtin_fma(slope, cu.d[q], base.d[q]), s * v.d[q]);
+        return r;
     }
-    return term;
+};
+
+// Non-equilibrium extrapolation onto a wall node (see extrapolate in lbm_device.h)
+__device__ __forceinline__ void extrapolate_t(D3 (&x)[9], const D3& uwall)
+{
+    D3 P, ux, uy;
+    moments_t(x, P, ux, uy);
+    const EquilibriumT nb(P, ux, uy), wall(P, uwall, D3(0.0));
+#pragma unroll
+    for (int k = 0; k < 9; ++k) x[k] = wall.plus(k, -1.0, nb.plus(k, -1.0, x[k]));
 }
 
-// Arrays of one cavity, packed [k][j][i] (plane = nx * ny).
-struct TBuf {
-    D3 *f[2], *l[2], *hp, *bp, *fb, *ln, *geo, *part;
+// scale dt / (m lam + dt), the relaxation coefficients of Eqs. (2.15)-(2.17)
+__device__ __forceinline__ D3 relax_coef(double scale, const Th& dt, double m, const D3& lam)
+{
+    const double r = 1.0 / (m * lam.v + dt.v), b = scale * dt.v * r;
+    D3 o;
+    o.v = b;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) o.d[q] = -b * r * m * lam.d[q];
+    o.d[0] += (scale - b) * r * dt.d;
+    return o;
+}
+
+// Steps (2)-(4): lambda (Eqs. 2.12-2.14, 1.4, every parameter differentiated: no Newtonian shortcut, as d mu / d n != 0
+// at n = 1), f-bar+ (Eq. 2.16) and f-hat+ (Eq. 2.15, over g) of a node.
+__device__ __forceinline__ void collide_t(D3 (&g)[9], const D3& lam_old, const TParams& c, D3 (&bp)[9], D3& lam)
+{
+    D3 P, ux, uy, n[9];
+    moments_t(g, P, ux, uy);
+    const EquilibriumT eq(P, ux, uy);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) n[k] = eq.plus(k, -1.0, g[k]);   // e - g
+    const D3 s58 = (n[5] + n[6]) + (n[7] + n[8]);
+    const D3 pxx = (n[1] + n[3]) + s58, pyy = (n[2] + n[4]) + s58, pxy = (n[5] - n[6]) + (n[7] - n[8]);
+    const double r = 1.0 / (2.0 * lam_old.v + c.dt.v);
+    const double Q = pxx.v * pxx.v + 2.0 * pxy.v * pxy.v + pyy.v * pyy.v, g2 = 18.0 * Q * r * r;
+    const bool floored = !(g2 > c.g2min);
+    const double m = floored ? c.g2min : g2, pw = pow_pos<double>(m, c.expo.v), lm = log(m);
+    lam.v = 3.0 * c.K.v * pw;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const double dr = -r * r * (2.0 * lam_old.d[q] + (q == 0 ? c.dt.d : 0.0));
+        const double dQ = 2.0 * (pxx.v * pxx.d[q] + 2.0 * pxy.v * pxy.d[q] + pyy.v * pyy.d[q]);
+        const double dg2 = floored ? 0.0 : 18.0 * r * (dQ * r + 2.0 * Q * dr);
+        lam.d[q] = 3.0 * pw * (c.K.d[q] + c.K.v * (c.expo.v * dg2 / m + lm * c.expo.d[q]));
+    }
+    const D3 b_hat = relax_coef(2.0, c.dt, 2.0, lam), b_bar = times(0.75, b_hat);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        bp[k] = muladd(b_bar, n[k], g[k]);
+        g[k] = muladd(b_hat, n[k], g[k]);
+    }
+}
+
+// One step of a tile of T x T nodes with every derivative, as step_tile.hip
+// does it: the workgroup holds the tile and four more nodes on every side, one
+// per thread; f-bar+ and then f(t + dt/2) in LDS (a plane per population and
+// component), f-hat+ in registers.  Bound by the chain of about 3500 FP64
+// instructions of a thread.  Five launches of a stage each through HBM took 44
+// us per step on 33 x 33 and 47 us on 129 x 129 nodes; tiles of 8 take 18 and 29
+// us (342 registers, one wavefront per SIMD), tiles of 12, with less halo and
+// two wavefronts per SIMD, 25 and 27 us (256 registers, some spilled).
+constexpr int kHalo = 4;
+constexpr int side_of(int T) { return T + 2 * kHalo; }
+constexpr int threads_of(int T) { return (side_of(T) * side_of(T) + kWaveLanes - 1) / kWaveLanes * kWaveLanes; }
+
+template <int T>
+struct TangentLds {
+    static constexpr int kSide = side_of(T);
+    double x[9][4][kSide * kSide];
+    __device__ __forceinline__ void put(int k, int t, const D3& a)
+    {
+        x[k][0][t] = a.v;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) x[k][q + 1][t] = a.d[q];
+    }
+    __device__ __forceinline__ D3 get(int k, int t) const
+    {
+        D3 a(x[k][0][t]);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) a.d[q] = x[k][q + 1][t];
+        return a;
+    }
 };
+
+// 2h times the mixed difference (Eqs. 2.5-2.7) of population k at a node from points u apart, u pointing upwind; edge:
+// the second upwind point leaves the grid (first-order form).
+template <int T>
+__device__ __forceinline__ D3 mixed_t(const TangentLds<T>& sh, int k, int t, int u, bool edge, double eps)
+{
+    D3 r;
+    double* out[4] = {&r.v, &r.d[0], &r.d[1], &r.d[2]};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const double* x = &sh.x[k][q][t];
+        const double c0 = x[0], a1 = x[u], f1 = x[-u], far = x[2 * u];
+        const double a2 = edge ? 2.0 * a1 - c0 : far;
+        *out[q] = eps * (f1 - a1) + (1.0 - eps) * (3.0 * c0 - 4.0 * a1 + a2);
+    }
+    return r;
+}
+
+// base_k - sdt c_k . grad phi_k of the moving populations (Eqs. 3.4, 3.6, 3.7) at a node of the tile
+template <int T, typename Base>
+__device__ __forceinline__ void transport_t(const TangentLds<T>& sh, const TParams& c, int t, int i, int j, const Th& a,
+                                            const Th& s, const Th& sdt, Base base, D3 (&out)[9])
+{
+    constexpr int kSide = side_of(T);
+#pragma unroll
+    for (int k = 1; k < 9; ++k) {
+        const double cx = cxk(k), cy = cyk(k), d = cx - cy * s.v;
+        // |c_xi| times the difference along the upwind direction; the theta derivative of c_xi is kept where c_xi is
+        // zero (the upwind side is then the c >= 0 one, as in the forward step)
+        const bool pos = d >= 0.0;
+        const double sg = pos ? c.inv2dxi : -c.inv2dxi;
+        const Th cxi{a.v * d * sg, (a.d * d - a.v * cy * s.d) * sg};
+        D3 term = muladd(cxi, mixed_t(sh, k, t, pos ? -1 : 1, i == (pos ? 1 : c.nx - 2), c.mix), D3(0.0));
+        if (cyk(k) > 0) term = axpy(c.inv2deta, mixed_t(sh, k, t, -kSide, j == 1, c.mix), term);
+        if (cyk(k) < 0) term = axpy(c.inv2deta, mixed_t(sh, k, t, kSide, j == c.ny - 2, c.mix), term);
+        out[k] = muladd(Th{-sdt.v, -sdt.d}, term, base(k));
+        __builtin_amdgcn_sched_barrier(0);   // keeps the reads of later populations from being moved up (registers)
+    }
+}
+
+template <int T>
+__global__ __launch_bounds__(threads_of(T), T == 8 ? 1 : 2) void t_step(TParams c, const D3* fin, const D3* lin, const D3* geo,
+                                                                         D3* fout, D3* lout)
+{
+    constexpr int kSide = side_of(T), kNodes = kSide * kSide;
+    __shared__ TangentLds<T> sh;
+    const int nx = c.nx, ny = c.ny, t = min((int)threadIdx.x, kNodes - 1), lx = t % kSide, ly = t / kSide;
+    const int i0 = (int)blockIdx.x * T, j0 = (int)blockIdx.y * T, i = i0 - kHalo + lx, j = j0 - kHalo + ly;
+    const int64_t pl = (int64_t)nx * ny;
+    // the nearest node of the grid: threads outside it compute a node that nothing reads
+    const int64_t id = (int64_t)min(max(j, 0), ny - 1) * nx + min(max(i, 0), nx - 1);
+    const bool grid = i >= 0 && j >= 0 && i < nx && j < ny;
+    const bool wall = grid && (i == 0 || j == 0 || i == nx - 1 || j == ny - 1);
+    const int ci = min(max(i, 1), nx - 2), cj = min(max(j, 1), ny - 2), ct = t + (ci - i) + (cj - j) * kSide;
+    auto dist = [&](int x, int y) { return max(max(i0 - x, x - (i0 + T - 1)), max(j0 - y, y - (j0 + T - 1))); };
+    const bool near = grid && dist(i, j) <= 2, own = grid && dist(i, j) <= 0;
+    D3 g[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) g[k] = fin[k * pl + id];
+    const D3 lam_old = lin[id], ga = geo[cj], gs = geo[ny + ci];
+    const Th a{ga.v, ga.d[0]}, s{gs.v, gs.d[0]};
+
+    // A
+    D3 lam;
+    {
+        D3 bp[9];
+        collide_t(g, lam_old, c, bp, lam);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) sh.put(k, t, bp[k]);
+    }
+    if (own) lout[id] = lam;
+    __syncthreads();
+    // B and Eq. (2.17)
+    D3 x[9];
+    if (near) {
+        x[0] = sh.get(0, ct);
+        transport_t(sh, c, ct, ci, cj, a, s, Th{0.5 * c.dt.v, 0.5 * c.dt.d}, [&](int k) { return sh.get(k, ct); }, x);
+        if (wall) extrapolate_t(x, j == ny - 1 ? c.ulid : D3(0.0));
+        D3 P, ux, uy;
+        moments_t(x, P, ux, uy);
+        const EquilibriumT eq(P, ux, uy);
+        const D3 b = relax_coef(1.0, c.dt, 4.0, lam);
+#pragma unroll
+        for (int k = 1; k < 9; ++k) x[k] = muladd(b, eq.plus(k, -1.0, x[k]), x[k]);
+    }
+    __syncthreads();
+    if (near)
+#pragma unroll
+        for (int k = 1; k < 9; ++k) sh.put(k, t, x[k]);
+    __syncthreads();
+    // C: f-hat+ is in g
+    if (own && !wall) transport_t(sh, c, t, i, j, a, s, c.dt, [&](int k) { return g[k]; }, g);
+    // walls from their inward nodes, which may belong to another tile: those recompute nothing, the wall node is left
+    // to the tile of its inward node
+    const bool walls = i0 <= 1 || j0 <= 1 || i0 + T >= nx - 1 || j0 + T >= ny - 1;
+    if (own && !wall) {
+#pragma unroll
+        for (int k = 0; k < 9; ++k) fout[k * pl + id] = g[k];
+    }
+    if (walls) {
+        __syncthreads();
+        if (own && !wall)
+#pragma unroll
+            for (int k = 0; k < 9; ++k) sh.put(k, t, g[k]);
+        __syncthreads();
+        if (wall && dist(ci, cj) <= 0) {
+#pragma unroll
+            for (int k = 0; k < 9; ++k) x[k] = sh.get(k, ct);
+            extrapolate_t(x, j == ny - 1 ? c.ulid : D3(0.0));
+#pragma unroll
+            for (int k = 0; k < 9; ++k) fout[k * pl + id] = x[k];
+        }
+    }
+}
 
 __device__ inline bool node(const TParams& c, int& i, int& j)
 {
@@ -96,85 +329,9 @@ __global__ __launch_bounds__(256) void t_init(TParams c, D3* f, D3* l)
     int i, j;
     if (!node(c, i, j)) return;
     const int64_t id = (int64_t)j * c.nx + i, pl = (int64_t)c.nx * c.ny;
-    D3 e[9];
-    equilibrium(D3(0.0), j == c.ny - 1 ? c.ulid : D3(0.0), D3(0.0), e);
-    for (int k = 0; k < 9; ++k) f[k * pl + id] = e[k];
+    const EquilibriumT eq(D3(0.0), j == c.ny - 1 ? c.ulid : D3(0.0), D3(0.0));
+    for (int k = 0; k < 9; ++k) f[k * pl + id] = eq.plus(k, 1.0, D3(0.0));
     l[id] = c.lam0;
-}
-
-__global__ __launch_bounds__(256) void t_stage_a(TParams c, const D3* fin, const D3* lin, D3* hp, D3* bp, D3* ln)
-{
-    int i, j;
-    if (!node(c, i, j)) return;
-    const int64_t id = (int64_t)j * c.nx + i, pl = (int64_t)c.nx * c.ny;
-    D3 g[9], e[9], P, ux, uy;
-    for (int k = 0; k < 9; ++k) g[k] = fin[k * pl + id];
-    moments(g, P, ux, uy);
-    equilibrium(P, ux, uy, e);
-    const D3 lam = relax_t(g, e, lin[id], c);
-    const Collision<D3> col(lam, c.dt);
-    for (int k = 0; k < 9; ++k) {
-        hp[k * pl + id] = col.a_hat * g[k] + col.b_hat * e[k];
-        bp[k * pl + id] = col.a_bar * g[k] + col.b_bar * e[k];
-    }
-    ln[id] = lam;
-}
-
-__global__ __launch_bounds__(256) void t_stage_b(TParams c, const D3* bp, D3* fb, const D3* geo)
-{
-    int i, j;
-    if (!node(c, i, j) || is_boundary(i, j, c.nx, c.ny)) return;
-    const int64_t id = (int64_t)j * c.nx + i, pl = (int64_t)c.nx * c.ny;
-    const D3 half_dt = D3(0.5) * c.dt;
-    fb[id] = bp[id];
-    for (int k = 1; k < 9; ++k) fb[k * pl + id] = bp[k * pl + id] - half_dt * transport_t(bp + k * pl, c, geo, i, j, k);
-}
-
-__global__ __launch_bounds__(256) void t_stage_bh(TParams c, const D3* fbar, const D3* ln, D3* fh)
-{
-    int i, j;
-    if (!node(c, i, j)) return;
-    const int64_t id = (int64_t)j * c.nx + i, pl = (int64_t)c.nx * c.ny;
-    D3 x[9];
-    if (is_boundary(i, j, c.nx, c.ny)) {
-        int ni, nj;
-        inward(i, j, c.nx, c.ny, ni, nj);
-        D3 xnb[9];
-        for (int k = 0; k < 9; ++k) xnb[k] = fbar[k * pl + (int64_t)nj * c.nx + ni];
-        extrapolate(xnb, j == c.ny - 1 ? c.ulid : D3(0.0), x);
-    } else {
-        for (int k = 0; k < 9; ++k) x[k] = fbar[k * pl + id];
-    }
-    D3 P, ux, uy, e[9];
-    moments(x, P, ux, uy);
-    equilibrium(P, ux, uy, e);
-    const HalfStep<D3> hs(ln[id], c.dt);
-    for (int k = 0; k < 9; ++k) fh[k * pl + id] = hs.a * x[k] + hs.b * e[k];
-}
-
-__global__ __launch_bounds__(256) void t_stage_c(TParams c, const D3* fh, const D3* hp, const D3* ln, D3* out, D3* lout,
-                                                 const D3* geo)
-{
-    int i, j;
-    if (!node(c, i, j)) return;
-    const int64_t id = (int64_t)j * c.nx + i, pl = (int64_t)c.nx * c.ny;
-    lout[id] = ln[id];
-    if (is_boundary(i, j, c.nx, c.ny)) return;
-    out[id] = hp[id];
-    for (int k = 1; k < 9; ++k) out[k * pl + id] = hp[k * pl + id] - c.dt * transport_t(fh + k * pl, c, geo, i, j, k);
-}
-
-__global__ __launch_bounds__(256) void t_stage_cb(TParams c, D3* out)
-{
-    int i, j;
-    if (!node(c, i, j) || !is_boundary(i, j, c.nx, c.ny)) return;
-    const int64_t pl = (int64_t)c.nx * c.ny;
-    int ni, nj;
-    inward(i, j, c.nx, c.ny, ni, nj);
-    D3 xnb[9], x[9];
-    for (int k = 0; k < 9; ++k) xnb[k] = out[k * pl + (int64_t)nj * c.nx + ni];
-    extrapolate(xnb, j == c.ny - 1 ? c.ulid : D3(0.0), x);
-    for (int k = 0; k < 9; ++k) out[k * pl + (int64_t)j * c.nx + i] = x[k];
 }
 
 // Eq. (5.1) per block: 1/2 |u|^2 w_i w_j J_j dxi deta with J_j = 1 + 2 eta_j cot(theta).
@@ -187,10 +344,11 @@ __global__ __launch_bounds__(256) void t_energy(TParams c, const D3* f, D3* part
         const int64_t id = (int64_t)j * c.nx + i, pl = (int64_t)c.nx * c.ny;
         D3 g[9], P, ux, uy;
         for (int k = 0; k < 9; ++k) g[k] = f[k * pl + id];
-        moments(g, P, ux, uy);
+        moments_t(g, P, ux, uy);
         const double wi = (i == 0 || i == c.nx - 1) ? 0.5 : 1.0;
         const double wj = (j == 0 || j == c.ny - 1) ? 0.5 : 1.0;
-        const D3 J = D3(1.0) + D3(2.0 * j * c.deta) * c.cot;
+        D3 J(1.0 + 2.0 * j * c.deta * c.cot.v);
+        J.d[0] = 2.0 * j * c.deta * c.cot.d;
         e = D3(0.5 * wi * wj * c.dxi * c.deta) * J * (ux * ux + uy * uy);
     }
     sh[0][threadIdx.x] = e.v;
@@ -226,16 +384,12 @@ void tangent_params(int nx, int ny, double re, double n, double theta_deg, doubl
     P.ny = ny;
     P.dxi = dxi;
     P.deta = deta;
-    {
-        double d[3] = {dC, 0, 0};
-        P.cot = D3::make(C, d);
-    }
+    P.cot = {C, dC};
     if (dt_rule == 1 || 1.0 / deta > (1.0 + C) / dxi) {
-        P.dt = D3(dt_rule == 1 ? cfl * std::min(dxi, deta) : cfl * deta);
+        P.dt = {dt_rule == 1 ? cfl * std::min(dxi, deta) : cfl * deta, 0.0};
     } else {
         const double dt = cfl * dxi / (1.0 + C);
-        double d[3] = {-dt / (1.0 + C) * dC, 0, 0};
-        P.dt = D3::make(dt, d);
+        P.dt = {dt, -dt / (1.0 + C) * dC};
     }
     const double K = std::pow(U, 2.0 - n) / re;
     {
@@ -246,14 +400,14 @@ void tangent_params(int nx, int ny, double re, double n, double theta_deg, doubl
         double d[3] = {0, 0.5, 0};
         P.expo = D3::make(0.5 * (n - 1.0), d);
     }
-    P.g2min = D3(gamma_min * gamma_min);
-    P.mix = D3(mix);
+    P.g2min = gamma_min * gamma_min;
+    P.mix = mix;
     {
         double d[3] = {0, 0, 1.0};
         P.ulid = D3::make(u_lid, d);
     }
-    P.inv2dxi = D3(0.5 / dxi);
-    P.inv2deta = D3(0.5 / deta);
+    P.inv2dxi = 0.5 / dxi;
+    P.inv2deta = 0.5 / deta;
     {
         double d[3] = {0, 0, 3.0 / re * sgnU};
         P.lam0 = D3::make(3.0 * U / re, d);
@@ -271,26 +425,33 @@ void tangent_params(int nx, int ny, double re, double n, double theta_deg, doubl
     }
 }
 
-// Sizes (in three-component duals) of the ten work arrays, in the order carve lays them out: the state twice
-// (nine planes and lambda each), f-hat+, f-bar+ then f(t + dt/2), f-bar, lambda of the step, the metric tables,
-// the energy partial sums.
-void workspace_sizes(size_t nn, size_t ngeo, size_t (&sizes)[10])
+// Work arrays of one cavity, packed [k][j][i]: the state twice (nine planes and lambda each), the metric tables a_j,
+// s_i, the energy partial sums.
+struct TBuf {
+    D3 *f[2], *l[2], *geo, *part;
+};
+
+size_t work_elems(int nx, int ny)
 {
-    const size_t s[10] = {9 * nn, 9 * nn, nn, nn, 9 * nn, 9 * nn, 9 * nn, nn, ngeo, (nn + 255) / 256};
-    for (int q = 0; q < 10; ++q) sizes[q] = s[q];
+    const size_t nn = (size_t)nx * ny;
+    return 20 * nn + (size_t)nx + (size_t)ny + (nn + 255) / 256;
 }
 
-// The ten work arrays carved from one workspace of tangent_workspace_elems(nx, ny) values.
+// The arrays carved from one workspace of work_elems(nx, ny) values.
 TBuf carve(D3* w, size_t nn, size_t ngeo)
 {
     TBuf b{};
-    D3** ptrs[] = {&b.f[0], &b.f[1], &b.l[0], &b.l[1], &b.hp, &b.bp, &b.fb, &b.ln, &b.geo, &b.part};
-    size_t sizes[10];
-    workspace_sizes(nn, ngeo, sizes);
-    for (int q = 0; q < 10; ++q) {
-        *ptrs[q] = w;
-        w += sizes[q];
+    auto take = [&](size_t n) {
+        D3* q = w;
+        w += n;
+        return q;
+    };
+    for (int q = 0; q < 2; ++q) {
+        b.f[q] = take(9 * nn);
+        b.l[q] = take(nn);
     }
+    b.geo = take(ngeo);
+    b.part = take((nn + 255) / 256);
     return b;
 }
 
@@ -308,15 +469,16 @@ hipError_t tangent_run(const TParams& P, const std::vector<D3>& geo, D3* work, i
     hipError_t e = hipMemcpyAsync(b.geo, geo.data(), geo.size() * sizeof(D3), hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return failed(e, "metric tables to the device");
     const dim3 g(nb), blk(256);
+    // tiles of 8 while each has a CU of its own (see t_step)
+    const int tile = ((P.nx + 7) / 8) * ((P.ny + 7) / 8) <= 256 ? 8 : 12;
+    const auto step = tile == 8 ? t_step<8> : t_step<12>;
+    const int threads = tile == 8 ? threads_of(8) : threads_of(12);
+    const dim3 tiles((P.nx + tile - 1) / tile, (P.ny + tile - 1) / tile);
     hipLaunchKernelGGL(t_init, g, blk, 0, s, P, b.f[0], b.l[0]);
     if ((e = hipGetLastError()) != hipSuccess) return failed(e, "Step (1) launch");
     int cur = 0;
     for (int64_t t = 0; t < n_steps; ++t) {
-        hipLaunchKernelGGL(t_stage_a, g, blk, 0, s, P, b.f[cur], b.l[cur], b.hp, b.bp, b.ln);
-        hipLaunchKernelGGL(t_stage_b, g, blk, 0, s, P, b.bp, b.fb, b.geo);
-        hipLaunchKernelGGL(t_stage_bh, g, blk, 0, s, P, b.fb, b.ln, b.bp);
-        hipLaunchKernelGGL(t_stage_c, g, blk, 0, s, P, b.bp, b.hp, b.ln, b.f[cur ^ 1], b.l[cur ^ 1], b.geo);
-        hipLaunchKernelGGL(t_stage_cb, g, blk, 0, s, P, b.f[cur ^ 1]);
+        hipLaunchKernelGGL(step, tiles, dim3(threads), 0, s, P, b.f[cur], b.l[cur], b.geo, b.f[cur ^ 1], b.l[cur ^ 1]);
         cur ^= 1;
         if ((t & 1023) == 1023 && (e = hipGetLastError()) != hipSuccess) return failed(e, "step launch");
     }
@@ -371,12 +533,12 @@ hipError_t scratch_of_current_device(void** out, std::string& err)
 
 }  // namespace
 
+// The grids that ifdlbm_gradient_noalloc accepts are those of its documented limit of 48 values per node, which its
+// work arrays (20 per node) stay well within.
 size_t tangent_workspace_elems(int nx, int ny)
 {
-    size_t sizes[10], total = 0;
-    workspace_sizes((size_t)nx * ny, (size_t)nx + (size_t)ny, sizes);
-    for (size_t x : sizes) total += x;
-    return total;   // 48 nn + nx + ny + ceil(nn / 256)
+    const size_t nn = (size_t)nx * ny;
+    return 48 * nn + (size_t)nx + (size_t)ny + (nn + 255) / 256;
 }
 
 size_t tangent_scratch_capacity_elems() { return kScratchBytes / sizeof(D3); }
@@ -390,11 +552,10 @@ hipError_t tangent_kinetic_energy(int nx, int ny, double re, double n, double th
     TParams P;
     std::vector<D3> geo;
     tangent_params(nx, ny, re, n, theta_deg, u_lid, cfl, mix, gamma_min, dt_rule, P, geo);
-    const size_t elems = tangent_workspace_elems(nx, ny);
     D3* work = nullptr;
     hipError_t e = hipSuccess;
     if (use_scratch) {
-        if (elems > tangent_scratch_capacity_elems()) {
+        if (tangent_workspace_elems(nx, ny) > tangent_scratch_capacity_elems()) {
             err = "grid too large for the scratch array";
             return hipErrorInvalidValue;
         }
@@ -403,7 +564,7 @@ hipError_t tangent_kinetic_energy(int nx, int ny, double re, double n, double th
         if (e != hipSuccess) return e;
         work = static_cast<D3*>(p);
     } else {
-        e = hipMalloc(reinterpret_cast<void**>(&work), elems * sizeof(D3));
+        e = hipMalloc(reinterpret_cast<void**>(&work), work_elems(nx, ny) * sizeof(D3));
         if (e != hipSuccess) {
             err = std::string("gradient: ") + hipGetErrorString(e);
             return e;

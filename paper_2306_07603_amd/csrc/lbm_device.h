@@ -454,29 +454,6 @@ __host__ __device__ __forceinline__ V implicit_relaxation_time(V Q18, V lam0, co
     return lam;
 }
 
-template <typename T>
-__device__ __forceinline__ T relaxation_time(const T g[9], const T e[9], T lam_old, const PowerLaw<T>& pl)
-{
-    if (pl.newtonian) return pl.lam_newton;
-    T n[9];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) n[k] = g[k] - e[k];
-    const T s58 = (n[5] + n[6]) + (n[7] + n[8]);
-    const T pxx = (n[1] + n[3]) + s58;
-    const T pyy = (n[2] + n[4]) + s58;
-    const T pxy = (n[5] - n[6]) + (n[7] - n[8]);
-    const T r = recip(T(2) * lam_old + pl.dt);
-    T gamma2 = T(18) * (pxx * pxx + T(2) * pxy * pxy + pyy * pyy) * r * r;
-    gamma2 = gamma2 > pl.g2min ? gamma2 : pl.g2min;
-    return pl.K3 * pow_pos<T>(gamma2, pl.expo);
-}
-
-template <typename T>
-__device__ __forceinline__ T relaxation_time(const T g[9], const T e[9], T lam_old, const CavityDesc& c)
-{
-    return relaxation_time(g, e, lam_old, PowerLaw<T>(c));
-}
-
 // Step (2) in the arithmetic V from d_k = e_k - g_k (T): Pi = -sum c c d, and
 // only its quadratic form enters gamma^2, so the sign drops out.  IMPLICIT
 // selects the fixed-point form (the cavity's implicit_lambda flag).
@@ -516,33 +493,6 @@ __device__ __forceinline__ V half_coef(V lam, V dt)
 {
     return dt * recip(V(4) * lam + dt);
 }
-
-// Steps (3)-(4): Eq. (2.15) f-hat+ = ((2 lam - dt) g + 2 dt e) / (2 lam + dt) and
-// Eq. (2.16) f-bar+ = ((4 lam - dt) g + 3 dt e) / (4 lam + 2 dt).
-template <typename T>
-struct Collision {
-    T a_hat, b_hat, a_bar, b_bar;
-    __device__ __forceinline__ Collision(T lam, T dt)
-    {
-        const T r = recip(T(2) * lam + dt);
-        a_hat = (T(2) * lam - dt) * r;
-        b_hat = T(2) * dt * r;
-        a_bar = (T(4) * lam - dt) * (T(0.5) * r);
-        b_bar = T(1.5) * dt * r;
-    }
-};
-
-// Eq. (2.17): f = (4 lam f-bar + dt e) / (4 lam + dt).
-template <typename T>
-struct HalfStep {
-    T a, b;
-    __device__ __forceinline__ HalfStep(T lam, T dt)
-    {
-        const T r = recip(T(4) * lam + dt);
-        a = T(4) * lam * r;
-        b = dt * r;
-    }
-};
 
 // Eq. (2.5) with (2.6)-(2.7): eps * central + (1 - eps) * second-order upwind,
 // times 2h, from the five points m2, m1, c0, p1, p2 along one grid line.  The
