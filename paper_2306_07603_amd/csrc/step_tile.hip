@@ -271,7 +271,7 @@ __global__ __launch_bounds__(LX* LY / NPT, LX > 16 ? 4 : 1) void k_tile(StepArgs
     __shared__ typename Storage<PREC>::T tile[9][LX * LY];
     const StripItem it = items[w0 + (int)blockIdx.x];
     if (it.unit < 0) return;   // padding of a per-XCD queue
-    const CavityDesc& c = a.desc[it.cav];
+    const CavityDesc c = a.desc[it.cav];
     double acc[kPartials];
 #pragma unroll
     for (int q = 0; q < kPartials; ++q) acc[q] = 0.0;
