@@ -2,6 +2,7 @@
 // initialisation, the residual reduction of Eq. (2.19), macroscopic output
 // (Eqs. 2.10-2.11), checkpoint conversion and the kinetic energy of Eq. (5.1).
 #include "ifdlbm_internal.h"
+#include "step_common.h"
 
 namespace ifd {
 namespace {
@@ -33,32 +34,32 @@ __global__ __launch_bounds__(kNodeBlock) void k_init(void* fv, void* lv, const C
 __global__ __launch_bounds__(256) void k_reduce(const double* partial, const int32_t* first, const int32_t* count,
                                                 const CavityDesc* desc, double* ref, double* out)
 {
-    __shared__ double sh[kPartials][256];
-    const int c = blockIdx.x;
+    __shared__ double sums[256 / kWaveLanes][kPartials];
+    const int c = blockIdx.x, t = threadIdx.x, n = count[c], u0 = first[c];
     double v[kPartials];
 #pragma unroll
     for (int q = 0; q < kPartials; ++q) v[q] = 0.0;
-    for (int u = threadIdx.x; u < count[c]; u += 256)
+    for (int u = t; u < n; u += 256)
 #pragma unroll
-        for (int q = 0; q < kPartials; ++q) v[q] += partial[(int64_t)(first[c] + u) * kPartials + q];
-#pragma unroll
-    for (int q = 0; q < kPartials; ++q) sh[q][threadIdx.x] = v[q];
+        for (int q = 0; q < kPartials; ++q) v[q] += partial[(int64_t)(u0 + u) * kPartials + q];
+    const double ws = wave_sums(v);
+    if (t % kWaveLanes < kPartials) sums[t / kWaveLanes][t % kWaveLanes] = ws;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
+    if (t >= kWaveLanes) return;
+    double s = 0.0;
+    if (t < kPartials)
 #pragma unroll
-            for (int q = 0; q < kPartials; ++q) sh[q][threadIdx.x] += sh[q][threadIdx.x + w];
-        __syncthreads();
-    }
+        for (int w = 0; w < 256 / kWaveLanes; ++w) s += sums[w][t];
     double* o = out + (int64_t)c * kResult;
-    if (threadIdx.x < kPartials) o[threadIdx.x] = sh[threadIdx.x][0];
-    if (threadIdx.x == 0) {
+    if (t < kPartials) o[t] = s;
+    const double sd = __shfl(s, 4, kWaveLanes), sp = __shfl(s, 5, kWaveLanes);
+    if (t == 0) {
         const double rd = ref[2 * c], rp = ref[2 * c + 1];
         o[kPartials] = rd;
         o[kPartials + 1] = rp;
-        if (count[c] == 0) return;   // a stopped cavity keeps its shifts
+        if (n == 0) return;   // a stopped cavity keeps its shifts
         const double nn = (double)desc[c].nx * (double)desc[c].ny;
-        const double md = rd + sh[4][0] / nn, mp = rp + sh[5][0] / nn;
+        const double md = rd + sd / nn, mp = rp + sp / nn;
         if (isfinite(md) && isfinite(mp)) {
             ref[2 * c] = md;
             ref[2 * c + 1] = mp;

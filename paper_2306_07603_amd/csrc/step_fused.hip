@@ -741,14 +741,8 @@ __global__ __launch_bounds__(kWaveLanes, Tuning<PREC>::kWaves) void k_fused(Step
     for (int q = 0; q < kPartials; ++q) acc[q] = 0.0;
     March<PREC, RES, IMPL>(a, it, c, sh, acc);
     if (RES) {
-        // wavefront sum in a fixed order
-#pragma unroll
-        for (int q5 = 0; q5 < kPartials; ++q5) {
-            double v = acc[q5];
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, kWaveLanes);
-            if (threadIdx.x == 0) a.partial[(int64_t)it.unit * kPartials + q5] = v;
-        }
+        const double s = wave_sums(acc);
+        if (threadIdx.x < kPartials) a.partial[(int64_t)it.unit * kPartials + threadIdx.x] = s;
     }
 }
 

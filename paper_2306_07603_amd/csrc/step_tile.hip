@@ -283,13 +283,8 @@ __global__ __launch_bounds__(LX* LY / NPT, LX > 16 ? 4 : 1) void k_tile(StepArgs
         // sum of each wavefront, then of the wavefronts, in a fixed order
         __shared__ double sums[NT / kWaveLanes][kPartials];
         const int t = threadIdx.x;
-#pragma unroll
-        for (int q = 0; q < kPartials; ++q) {
-            double s = acc[q];
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, kWaveLanes);
-            if (t % kWaveLanes == 0) sums[t / kWaveLanes][q] = s;
-        }
+        const double ws = wave_sums(acc);
+        if (t % kWaveLanes < kPartials) sums[t / kWaveLanes][t % kWaveLanes] = ws;
         __syncthreads();
         if (t < kPartials) {
             double s = 0.0;
