@@ -413,9 +413,16 @@ int enqueue_probe(ifdlbm_s* h)
 
 bool is_residual_step(const ifdlbm_s* h, int64_t step_index) { return (step_index + 1) % h->opt.residual_every == 0; }
 
+// Whether the storage mode rounds stochastically: only then does a call or a replay advance the random-word counter
+// (a launch of its own, 1.3 to 4 us).
+bool draws_words(const ifdlbm_s* h)
+{
+    return h->opt.precision == P_FP32SR || h->opt.precision == P_FP32SRF || h->opt.precision == P_FP16DEV;
+}
+
 int eager_steps(ifdlbm_s* h, int64_t n)
 {
-    if (n > 0) {
+    if (n > 0 && draws_words(h)) {
         hipError_t e = launch_seed_bump(h->d_seed, h->stream);
         if (e != hipSuccess) return fail(IFDLBM_EDEVICE, std::string("seed: ") + hipGetErrorString(e));
     }
@@ -447,7 +454,7 @@ int build_graph(ifdlbm_s* h)
     hipGraph_t graph = nullptr;
     IFD_HIP(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
     int rc = IFDLBM_OK;
-    if (launch_seed_bump(h->d_seed, h->stream) != hipSuccess) rc = fail(IFDLBM_EDEVICE, "seed bump in capture");
+    if (draws_words(h) && launch_seed_bump(h->d_seed, h->stream) != hipSuccess) rc = fail(IFDLBM_EDEVICE, "seed bump in capture");
     for (int s = 0; s < G && rc == IFDLBM_OK; ++s) {
         rc = enqueue_step(h, is_residual_step(h, s), (uint32_t)s);
         h->cur ^= 1;
@@ -1182,9 +1189,8 @@ static int ifdlbm_adjoint_impl(const ifdlbm_cavity* cav, const ifdlbm_options* o
     };
     // One step from a raw state to the next.  Every step draws the random words of a call of its own, so that a
     // segment recomputed with its counter restored stores the same bits.
-    const bool draws = prec == P_FP32SR || prec == P_FP32SRF || prec == P_FP16DEV;
     auto step = [&](const char* from, char* to) {
-        if (draws && !hip_ok(launch_seed_bump(h->d_seed, s), "seed")) return;
+        if (draws_words(h) && !hip_ok(launch_seed_bump(h->d_seed, s), "seed")) return;
         StepArgs a = step_args(h);
         a.f_in = from;
         a.l_in = from + fslot;
