@@ -11,7 +11,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libifdlbm.so")
-SOURCES = ["api.hip", "kernels_common.hip", "step_staged.hip", "step_fused.hip", "step_tile.hip", "gradient.hip", "adjoint.hip", "regime.cpp"]
+SOURCES = ["api.hip", "kernels_common.hip", "step_staged.hip", "step_fused.hip", "step_tile.hip", "step_block.hip",
+           "gradient.hip", "adjoint.hip", "regime.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -21,13 +22,13 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-parameter",
 ]
-# Flags of single sources.  The march kernel is scheduled for instruction-level parallelism (LLVM's iterative-ilp
-# strategy) instead of occupancy first: it keeps its occupancy either way (two waves per SIMD with FP32 arithmetic, one
-# with FP64), and that schedule measured faster in every storage mode (FP64 +6 %, FP16DEV +3.4 %, FP32SRF +1.6 %, FP32
-# +0.8 % over the default).  Both kernels of the fused schedule are compiled with contraction limited to single
-# expressions: what is fused is then fixed by the source, and the two round a node alike.
+# Flags of single sources.  The FP32 march kernel is scheduled for instruction-level parallelism (LLVM's iterative-ilp
+# strategy) instead of occupancy first: it keeps its two waves per SIMD either way, and that schedule measured faster in
+# every storage mode (FP16DEV +3.4 %, FP32SRF +1.6 %, FP32 +0.8 % over the default).  The kernels of the fused schedule
+# are compiled with contraction limited to single expressions: what is fused is then fixed by the source, and they round
+# a node alike.
 FILE_FLAGS = {"step_fused.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp", "-ffp-contract=on"],
-              "step_tile.hip": ["-ffp-contract=on"]}
+              "step_tile.hip": ["-ffp-contract=on"], "step_block.hip": ["-ffp-contract=on"]}
 
 
 def source_files():

@@ -59,12 +59,16 @@ namespace {
 constexpr double kCs2 = 1.0 / 3.0;
 
 // Rows per segment of the fused kernel's work items (the columns per strip
-// are at most kStripOut).  Automatic choice: the longest segment (fewest
+// are at most kStripOut).  Automatic choice, FP32 arithmetic: the longest segment (fewest
 // recomputed halo rows) that still gives kTargetItems work items, so that the
 // GPU stays full through the tail of a launch; the shortest otherwise.
+// FP64 arithmetic: plan_block.
 constexpr int kSegCandidates[] = {128, 96, 80, 72, 64, 56, 48, 40, 32, 24, 16, 8};
 constexpr int kTargetItems = 4096;
 constexpr int kXcds = 8;   // MI355X: workgroups are dealt to the 8 XCDs in turn
+constexpr int64_t kCus = 256;
+constexpr int kBlockWaves = 4;                         // rows of a chunk of the FP64 march (step_block.hip)
+constexpr int64_t kBlockSlots = 2 * kCus / kXcds;      // its workgroups that run on an XCD at a time
 
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
@@ -182,23 +186,67 @@ int segment_start(int g, int ng, int ny)
     return r <= 2 ? b - r : b + (5 - r);
 }
 
+// Segment length of the FP64 march (step_block.hip) for one launch, and its cost: the chunks of rows that one of an
+// XCD's places runs in turn (two workgroups per CU; whole groups of strips go to one XCD, the longest items first, see
+// order_for_batch), in whole items of the shortest kind.  A chunk takes 4.5 .. 5.8 us wherever it was measured, so a
+// full last turn counts for more than the halo (513^2 x 12: 480 items of 129 rows 196 us, 1560 items of 40 rows 206;
+// 257^2 x 24: 480 of 65 rows 101, 720 of 43 rows 118; 1025^2: 24 segments, three groups of 19 strips per XCD, 62, 26
+// segments 86; 65^2 x 60, 129^2 x 57, 257^2 x 75 and 513^2 x 64 in one batch: at most 132 rows 1249, 100 rows 1272, 52
+// rows 1284).
+struct BlockPlan {
+    int rows = 8;
+    double cost = 0.0;
+};
+
+BlockPlan plan_block(const ifdlbm_s* h, int one_cav)
+{
+    BlockPlan best;
+    for (int seg = 136; seg >= 8; seg -= 4) {
+        int64_t groups = 0, items = 0, chunks = 0, shortest = INT64_MAX, longest = 0;
+        for (int c = std::max(one_cav, 0); c < (one_cav < 0 ? h->n_cav : one_cav + 1); ++c) {
+            const CavityDesc& d = h->desc[c];
+            if (!d.active) continue;
+            const int64_t ng = ceil_div(d.ny, seg), n = ng * ceil_div(d.nx, kStripOut);
+            const int64_t len = ceil_div(ceil_div(d.ny, (int)ng) + 8, kBlockWaves);
+            groups += ng;
+            items += n;
+            chunks += n * len;
+            shortest = std::min(shortest, len);
+            longest = std::max(longest, len);
+        }
+        if (items == 0) break;
+        const int64_t queue = ((groups + kXcds - 1) / kXcds * items + groups - 1) / groups;
+        const double turns = (double)queue / kBlockSlots * ((double)chunks / (double)items) / (double)shortest;
+        const double cost = std::max(std::ceil(turns - 1e-9) * (double)shortest, (double)longest);
+        if (best.cost == 0.0 || cost < best.cost) best = {seg, cost};
+    }
+    return best;
+}
+
 // Kernel of the fused schedule for one launch (all running cavities, or cavity one_cav alone): a tile shape of
-// step_tile.hip, or kMarch, the row march of step_fused.hip.  A march item is a chain of at least 16 rows (35 us in
-// FP32, 43 us in FP64, however small the cavity), a tile a chain of one node per stage; but tiles recompute more halo,
-// so the march wins once its items fill the GPU.  Microseconds per step, march against tile shapes 0, 1, 2 (side x
-// cavities; FP32SRF, then FP64):
-//   33 x 1     35.0 /  5.2   5.7   7.9     43.4 /  5.7   7.4   9.5
-//   65 x 4     35.5 /  5.9   6.0   8.9     43.3 /  7.5   7.9  11.1
-//   65 x 8     35.2 /  7.2   6.4   9.0     43.5 / 10.9   8.7  11.3
-//   193 x 2    35.6 / 10.3   8.3   9.6     44.2 / 15.8  11.8  12.1
-//   129 x 6    36.5 / 12.4  11.3   9.8     44.9 / 19.5  15.2  12.6
-//   193 x 4    37.2 / 15.7  13.4  12.5     45.0 / 25.5  18.0  20.6
-//   513 x 2    37.8 / 37.7  29.2  25.7     62.9 / 72.5  40.8  43.5
-//   513 x 4    54.9 / 67.2  52.6  37.5     96.4 /  132  71.0  68.8
-//   513 x 12    120 /  191   150  94.8      255 /  465   248   227
-//   513 x 16    149 /  307   230   146      289 /  618   330   299
+// step_tile.hip, or kMarch, the march of the storage mode's arithmetic.  A march item is a chain of rows (35 us in
+// FP32 at 16 of them, however small the cavity), a tile a chain of one node per stage; but tiles recompute more halo,
+// so the march wins once its items fill the GPU.  Microseconds per step of tile shapes 0, 1, 2 and the march (side x
+// cavities; FP32SRF, then FP64; the FP64 march at its planned segment length):
+//   33 x 1      5.2   5.7   7.9   35.0      5.7   7.4   9.5
+//   65 x 4      5.9   6.0   8.9   35.5      7.5   7.9  11.1
+//   65 x 8      7.2   6.4   9.0   35.2     10.9   8.7  11.3
+//   193 x 2    10.3   8.3   9.6   35.6     15.8  11.8  12.1
+//   129 x 6    12.4  11.3   9.8   36.5     19.5  15.2  12.6
+//   193 x 4    15.7  13.4  12.5   37.2     25.5  18.0  20.6
+//   129 x 20                                     34.1         35.2
+//   513 x 2    37.7  29.2  25.7   37.8     72.5  40.8  43.5   38.6
+//   129 x 40                                     59.2         50.8
+//   65 x 200                                           77.5   90.6
+//   513 x 4    67.2  52.6  37.5   54.9      132  71.0  68.8   61.1
+//   33 x 900                                            129   98.0
+//   513 x 12    191   150  94.8    120      465   248   227    197
+//   513 x 16    307   230   146    149      618   330   299    261
 // Shapes 0 and 1 stay ahead while they have at most two workgroups per CU.  In FP64 shape 2 has room for one workgroup
-// per CU only: a second round of it loses to shape 1 until there are about six.
+// per CU only: a second round of it loses to shape 1 until there are about six; a round of shape 1 (two workgroups per
+// CU) takes 6.3 .. 7.7 us beyond some five rounds, a round of shape 2 10.0 .. 11.0 us, a chunk and round of the march
+// 4.5 .. 5.3 us at these sizes.  Which of them is least follows the grids, not the node count alone (a strip of a 65
+// wide cavity uses 33 of its 64 lanes), so the three are compared.
 constexpr int kMarch = -1;
 
 int choose_kernel(const ifdlbm_s* h, int one_cav = -1)
@@ -211,16 +259,18 @@ int choose_kernel(const ifdlbm_s* h, int one_cav = -1)
         nodes += (int64_t)d.nx * d.ny;
         for (int s = 0; s < kTileShapes; ++s) tiles[s] += (int64_t)ceil_div(d.nx, kTileCols[s]) * ceil_div(d.ny, kTileRows[s]);
     }
-    constexpr int64_t kCus = 256;
     if (tiles[0] <= 2 * kCus) return 0;
     if (tiles[1] <= 2 * kCus) return 1;
     const int prec = h->opt.precision;
-    const bool wide = t_elem_size(prec) == 8;
-    // nodes up to which shape 2 is ahead of the march (513 x 512 cavities: FP64 13, FP32SRF 16, FP32 11, FP16DEV 24 and
+    if (t_elem_size(prec) == 8) {
+        const int shape = tiles[2] > kCus && tiles[2] < 6 * kCus ? 1 : 2;
+        const double tile = shape == 1 ? 6.9 * (double)tiles[1] / (2 * kCus) : 10.1 * (double)tiles[2] / kCus;
+        return 4.8 * plan_block(h, one_cav).cost < tile ? kMarch : shape;
+    }
+    // nodes up to which shape 2 is ahead of the march (513 x 512 cavities: FP32SRF 16, FP32 11, FP16DEV 24 and
     // more: its 44 bytes per node leave it bound by instructions, which four wavefronts per SIMD issue faster)
-    const int64_t most = wide ? 3500000 : prec == P_FP32SRF ? 4000000 : prec == P_FP32 ? 3000000 : 8000000;
-    if (nodes > most) return kMarch;
-    return wide && tiles[2] > kCus && tiles[2] < 6 * kCus ? 1 : 2;
+    const int64_t most = prec == P_FP32SRF ? 4000000 : prec == P_FP32 ? 3000000 : 8000000;
+    return nodes > most ? kMarch : 2;
 }
 
 // Rows per segment for the cavities of one launch: all running cavities (one_cav < 0, batched launch) or
@@ -228,6 +278,7 @@ int choose_kernel(const ifdlbm_s* h, int one_cav = -1)
 int segment_rows(const ifdlbm_s* h, int one_cav = -1)
 {
     if (h->opt.segment_rows > 0) return h->opt.segment_rows;
+    if (t_elem_size(h->opt.precision) == 8) return plan_block(h, one_cav).rows;
     for (int seg : kSegCandidates) {
         size_t n = 0;
         for (int c = 0; c < h->n_cav; ++c)
@@ -305,7 +356,8 @@ int rebuild_worklists(ifdlbm_s* h)
                 const bool march = shape == kMarch;
                 const int ns = ceil_div(d.nx, march ? kStripOut : kTileCols[shape]);
                 const int ng = ceil_div(d.ny, march ? seg : kTileRows[shape]);
-                auto row = [&](int g) { return march ? segment_start(g, ng, d.ny) : (int)((int64_t)g * d.ny / ng); };
+                const bool mod5 = march && t_elem_size(h->opt.precision) == 4;   // the unrolled march
+                auto row = [&](int g) { return mod5 ? segment_start(g, ng, d.ny) : (int)((int64_t)g * d.ny / ng); };
                 for (int g = 0; g < ng; ++g)
                     for (int s = 0; s < ns; ++s)
                         h->act_items.push_back({c, (int16_t)(s * d.nx / ns), (int16_t)((s + 1) * d.nx / ns), row(g),
@@ -366,6 +418,7 @@ StepArgs step_args(ifdlbm_s* h)
 hipError_t launch_items(int shape, int prec, bool impl, const StepArgs& a, const StripItem* items, int w0, int nw,
                         bool residual, hipStream_t s)
 {
+    if (shape == kMarch && t_elem_size(prec) == 8) return launch_block_step(prec, impl, a, items, w0, nw, residual, s);
     return shape == kMarch ? launch_fused_step(prec, impl, a, items, w0, nw, residual, s)
                            : launch_tile_step(shape, prec, impl, a, items, w0, nw, residual, s);
 }
@@ -1036,7 +1089,7 @@ static int ifdlbm_autotune_impl(ifdlbm_t* h, int32_t steps_per_trial, int32_t* s
         return e;
     };
     if (!rc && save() != hipSuccess) rc = fail(IFDLBM_EDEVICE, "autotune: state backup");
-    int best = 0;       // rows per item of the fastest kernel, and the option that selects it (0: the automatic tile)
+    int best = 0;       // rows per item of the fastest kernel, and the option that selects it (0: the automatic choice)
     int32_t best_opt = rows0;
     float best_ms = 0.0f;
     const int rec_every = h->rec_every;
@@ -1048,7 +1101,9 @@ static int ifdlbm_autotune_impl(ifdlbm_t* h, int32_t steps_per_trial, int32_t* s
         if (seg <= max_ny || seg == kSegCandidates[sizeof(kSegCandidates) / sizeof(kSegCandidates[0]) - 1]) trials.push_back(seg);
     h->opt.segment_rows = 0;
     const int tile = choose_kernel(h);
-    if (tile != kMarch && h->opt.batched) trials.push_back(0);
+    // the automatic kernel, where it is not one of the trials already
+    if ((tile != kMarch || t_elem_size(prec) == 8) && h->opt.batched) trials.push_back(0);
+    const int auto_rows = tile == kMarch ? plan_block(h, -1).rows : kTileRows[tile];
     for (int32_t seg : trials) {
         if (rc) break;
         h->opt.segment_rows = seg;
@@ -1061,7 +1116,7 @@ static int ifdlbm_autotune_impl(ifdlbm_t* h, int32_t steps_per_trial, int32_t* s
         float ms = 0.0f;
         if (!rc && hipEventElapsedTime(&ms, e0, e1) != hipSuccess) rc = fail(IFDLBM_EDEVICE, "hipEventElapsedTime");
         if (!rc && (best == 0 || ms < best_ms)) {
-            best = seg ? seg : kTileRows[tile];
+            best = seg ? seg : auto_rows;
             best_opt = seg;
             best_ms = ms;
         }

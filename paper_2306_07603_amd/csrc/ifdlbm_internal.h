@@ -78,8 +78,12 @@ hipError_t launch_seed_bump(uint32_t* ctr, hipStream_t s);
 hipError_t launch_staged_step(int prec, const StepArgs& a, const NodeBlock* blocks, int b0, int nb,
                               bool residual, hipStream_t s);
 
-// Fused schedule: one launch over the strip items [w0, w0 + nw).
+// Fused schedule: one launch over the strip items [w0, w0 + nw), by the march of the storage mode's arithmetic:
+// launch_fused_step for FP32 (step_fused.hip), launch_block_step for FP64 (step_block.hip).
 hipError_t launch_fused_step(int prec, bool implicit_lambda, const StepArgs& a, const StripItem* items, int w0, int nw,
+                             bool residual, hipStream_t s);
+
+hipError_t launch_block_step(int prec, bool implicit_lambda, const StepArgs& a, const StripItem* items, int w0, int nw,
                              bool residual, hipStream_t s);
 
 // Fused schedule, small batches: one workgroup per tile of output nodes (step_tile.hip).  Shape s holds tiles of at

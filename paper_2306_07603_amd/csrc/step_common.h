@@ -1,5 +1,5 @@
 // step_common.h -- difference stencils and residual sums shared by the kernels
-// of the fused schedule (step_fused.hip, step_tile.hip), so that both store
+// of the fused schedule (step_fused.hip, step_tile.hip, step_block.hip), so that all store
 // the same bits.
 #pragma once
 

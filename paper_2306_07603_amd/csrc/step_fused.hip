@@ -1,5 +1,5 @@
 // step_fused.hip -- one launch per IFDLBM time step (arXiv:2306.07603,
-// Section 4, Steps (2)-(6)); each wavefront reads the state of its work item
+// Section 4, Steps (2)-(6)) in FP32 arithmetic; each wavefront reads the state of its work item
 // once from HBM and writes it once.
 //
 // Work item: output columns [i0, i1) and rows [j0, j1) of one cavity.  The 64
@@ -17,8 +17,8 @@
 // xi-direction stencils read neighbour lanes through one LDS row per
 // population, at per-lane addresses that already point at the upwind side
 // (the sign of the contravariant velocity of Eq. (3.2) is fixed per column
-// and population), so no operand is selected after the read.  With FP32
-// arithmetic the LDS row holds backward differences of the values, each
+// and population), so no operand is selected after the read.  The LDS row
+// holds backward differences of the values, each
 // lane's taken across the wavefront from its left neighbour, and both
 // directions apply Eq. (2.5) to differences.  The stored f-hat that the
 // exact final update of FP32SRF adds at stage C comes from a lane-private
@@ -52,13 +52,8 @@ constexpr int kGxRing = 6;
 // populations per pass of the xi exchange through LDS
 constexpr int xs_rows(bool exact_final) { return exact_final ? 1 : 8; }
 
-// Waves per SIMD the register allocation must allow: two with FP32 arithmetic (256 VGPRs each), one with
-// FP64 arithmetic (its rings and stage temporaries take about 430 registers).
-template <int PREC>
-struct Tuning {
-    static constexpr bool kWide = sizeof(typename Storage<PREC>::T) == 8;
-    static constexpr int kWaves = kWide ? 1 : 2;
-};
+// Waves per SIMD the register allocation must allow (256 VGPRs each).
+constexpr int kMarchWaves = 2;
 
 // Dword 3 of a raw buffer resource on the gfx9 family (CDNA): 32-bit data
 // format, no swizzle, no index stride.
@@ -75,17 +70,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, uint3
 }
 
 template <typename F> struct Buf;
-template <> struct Buf<double> {
-    __device__ static double ld(__amdgpu_buffer_rsrc_t r, uint32_t vo, uint32_t so)
-    {
-        return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, vo, so, 0));
-    }
-    __device__ static void st(double v, __amdgpu_buffer_rsrc_t r, uint32_t vo, uint32_t so)
-    {
-        using W = decltype(__builtin_amdgcn_raw_buffer_load_b64(r, 0u, 0u, 0));
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(W, v), r, vo, so, 0);
-    }
-};
 template <> struct Buf<float> {
     __device__ static float ld(__amdgpu_buffer_rsrc_t r, uint32_t vo, uint32_t so)
     {
@@ -107,10 +91,6 @@ template <> struct Buf<__half> {
     }
 };
 
-template <typename T> __device__ __forceinline__ const T* geo_of(const StepArgs& a);
-template <> __device__ __forceinline__ const double* geo_of<double>(const StepArgs& a) { return a.geo; }
-template <> __device__ __forceinline__ const float* geo_of<float>(const StepArgs& a) { return a.geo32; }
-
 // x of lane l - 1 in lane l (lane 0 reads 0): a wavefront shift of the data-parallel primitives, folded by the
 // compiler into the instruction that uses it.
 __device__ __forceinline__ float lane_below(float x)
@@ -130,10 +110,7 @@ constexpr bool moves_down(int k) { return cyk(k) < 0; }
 // (2, 4), (5, 7), (6, 8) the second member has minus the first's d.  The
 // upwind side follows sign(d) (ties: the c >= 0 side; there |d| = 0 and the
 // term vanishes).  Byte offsets into an LDS row.
-// FP64 arithmetic (rows of values): a1/a2/f1 of the first member of each
-// pair, a2m the far point of the mirrored member (whose a1 and f1 are the
-// pair's f1 and a1); ad = |d|.
-// FP32 arithmetic (rows of backward differences B(m) = x(m) - x(m - 1)): the
+// On rows of backward differences B(m) = x(m) - x(m - 1) the
 // member with d >= 0 reads near B(l), far B(l - 1) and other B(l + 1), the
 // member with d < 0 near B(l + 1), far B(l + 2) and other B(l).  a1 is the
 // first member's near (the second's other), f1 the first's other (the
@@ -144,9 +121,8 @@ template <typename T>
 struct XiLane {
     uint32_t own;           // this lane's column
     uint32_t a1[3], a2[3], f1[3], a2m[3];
-    T ad[3];                // |d| of the pairs
+    T ad[3];                // d of the pairs
     bool edge1, edge3;      // second upwind point outside the grid (first-order point, Eq. 2.7 at walls)
-    bool edge_p[3], edge_m[3];
 
     __device__ __forceinline__ XiLane(int lane, int i, int nx, T s)
     {
@@ -156,22 +132,12 @@ struct XiLane {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const bool pos = d[c] >= T(0);
-            edge_p[c] = pos ? i == 1 : i == nx - 2;
-            edge_m[c] = pos ? i == nx - 2 : i == 1;
-            if constexpr (kDiffForm<T>) {
-                const uint32_t far_p = i == 1 ? own : own - E, far_m = i == nx - 2 ? own + E : own + 2 * E;
-                ad[c] = d[c];
-                a1[c] = pos ? own : own + E;
-                f1[c] = pos ? own + E : own;
-                a2[c] = pos ? far_p : far_m;
-                a2m[c] = pos ? far_m : far_p;
-            } else {
-                ad[c] = pos ? d[c] : -d[c];
-                a1[c] = pos ? own - E : own + E;
-                f1[c] = pos ? own + E : own - E;
-                a2[c] = pos ? own - 2 * E : own + 2 * E;
-                a2m[c] = pos ? own + 2 * E : own - 2 * E;
-            }
+            const uint32_t far_p = i == 1 ? own : own - E, far_m = i == nx - 2 ? own + E : own + 2 * E;
+            ad[c] = d[c];
+            a1[c] = pos ? own : own + E;
+            f1[c] = pos ? own + E : own;
+            a2[c] = pos ? far_p : far_m;
+            a2m[c] = pos ? far_m : far_p;
         }
         edge1 = i == 1;
         edge3 = i == nx - 2;
@@ -253,6 +219,7 @@ struct March {
     using V = typename S::V;
     using F = typename S::F;
     using L = typename S::L;
+    static_assert(kDiffForm<T>, "FP32 arithmetic: the FP64 modes take the march of step_block.hip");
 
     static constexpr int sg(int R, int d) { return (R + 2 * kRing - d) % kRing; }
     static constexpr int sf(int R, int d) { return (R + 3 * kRing - d) % kRing; }
@@ -283,8 +250,7 @@ struct March {
     T fh[kRing][9];        // f(t + dt/2) of rows t-6 .. t-2
     V lam[kRing];          // lambda of rows t-4 .. t
     // FP32SRF reads the metric a_j one row ahead into this ring (rows t-5 .. t-1, uniform): measured 1 % faster
-    // there, with identical results; 0.5 % slower in FP32, and in FP64 it moves one FMA grouping (1-ulp changes),
-    // so the other modes read a_j where they use it
+    // there, with identical results; 0.5 % slower in FP32, so the other modes read a_j where they use it
     static constexpr bool kMetricRing = S::kExactFinal;
     T am[kRing];
     F gn_[9];              // f-hat of row t + 1, in flight
@@ -295,7 +261,7 @@ struct March {
                                      double (&acc_)[kPartials])
         : a(a_), it(it_), c(c_), sh(sh_), acc(acc_), ref{0.0, 0.0}, pl(c_),
           xl(threadIdx.x, it_.i0 - kHaloCols + (int)threadIdx.x, c_.nx,
-             geo_of<T>(a_)[c_.geo_off + c_.ny + min(max(it_.i0 - kHaloCols + (int)threadIdx.x, 0), c_.nx - 1)])
+             a_.geo32[c_.geo_off + c_.ny + min(max(it_.i0 - kHaloCols + (int)threadIdx.x, 0), c_.nx - 1)])
     {
         lane = threadIdx.x;
         nx = c.nx;
@@ -318,7 +284,7 @@ struct March {
         sx_b = T(0.5) * dt * T(c.inv2dxi);
         sx_c = dt * T(c.inv2dxi);
         eps = T(c.mix);
-        geo = (const __attribute__((address_space(4))) T*)(geo_of<T>(a) + c.geo_off);
+        geo = (const __attribute__((address_space(4))) T*)(a.geo32 + c.geo_off);
         fpb = (uint32_t)c.plane * (uint32_t)sizeof(F);
         rf_in = buffer_of(static_cast<const F*>(a.f_in) + c.f_off, 9u * fpb);
         rf_out = buffer_of(static_cast<F*>(a.f_out) + c.f_off, 9u * fpb);
@@ -431,100 +397,50 @@ struct March {
             const int x = (k - 1) % kXsRows;
             if (x == 0) {
                 if (k > 1) wave_sync();   // the previous pass has read the rows
-                if constexpr (kDiffForm<T>) {
-                    // the backward difference of each lane's value, its left neighbour's taken across the wavefront
+                // the backward difference of each lane's value, its left neighbour's taken across the wavefront
 #pragma unroll
-                    for (int m = k; m < k + kXsRows; ++m)
-                        xs[m - k][lane + kPad] = ring[S2][m] - lane_below(ring[S2][m]);
-                } else {
-#pragma unroll
-                    for (int m = k; m < k + kXsRows; ++m) xs[m - k][lane + kPad] = ring[S2][m];
-                }
+                for (int m = k; m < k + kXsRows; ++m) xs[m - k][lane + kPad] = ring[S2][m] - lane_below(ring[S2][m]);
                 wave_sync();
             }
             const T* row = xs[x];
             const T c0 = ring[S2][k];
             constexpr uint32_t E = sizeof(T);
-            if constexpr (kDiffForm<T>) {
-                // xi term from the backward differences: near, far and other point of this population's upwind
-                // side (XiLane), signed by d
-                T n, f, o, w;
-                bool minus;   // out = base - w t (d >= 0 member of a pair, k = 1) or base + w t
-                if (k == 1 || k == 3) {
-                    const bool pos = k == 1;
-                    n = lds_at(row, pos ? xl.own : xl.own + E);
-                    f = (pos ? xl.edge1 : xl.edge3) ? n : lds_at(row, pos ? xl.own - E : xl.own + 2 * E);
-                    o = lds_at(row, pos ? xl.own + E : xl.own);
-                    w = T(1);
-                    minus = pos;
-                } else {
-                    const int pr = (k == 2 || k == 4) ? 0 : ((k == 5 || k == 7) ? 1 : 2);
-                    const bool first = k == 2 || k == 5 || k == 6;
-                    n = lds_at(row, first ? xl.a1[pr] : xl.f1[pr]);
-                    f = lds_at(row, first ? xl.a2[pr] : xl.a2m[pr]);
-                    o = lds_at(row, first ? xl.f1[pr] : xl.a1[pr]);
-                    w = xl.ad[pr];
-                    minus = first;
-                }
-                const T t = mx.apply_back(n, f, o);
-                T r = minus ? base[k] - w * t : base[k] + w * t;
-                // eta term: the backward differences along the upwind direction from the ring (the row below for
-                // populations moving up, the row above for those moving down); at rows 1 and ny - 2 the far one is
-                // the near one
-                if (moves_up(k)) {
-                    const T nb = c0 - ring[S1][k];
-                    r = my.sub_back(r, nb, elo ? nb : ring[S1][k] - ring[S0][k], ring[S3][k] - c0);
-                }
-                if (moves_down(k)) {
-                    const T nb = c0 - ring[S3][k];
-                    r = my.sub_back(r, nb, ehi ? nb : ring[S3][k] - ring[S4][k], ring[S1][k] - c0);
-                }
-                out[k] = r;
-                continue;
-            }
-            T a1, a2, f1, w;
-            bool edge = false;
+            // xi term from the backward differences: near, far and other point of this population's upwind
+            // side (XiLane), signed by d
+            T n, f, o, w;
+            bool minus;   // out = base - w t (d >= 0 member of a pair, k = 1) or base + w t
             if (k == 1 || k == 3) {
                 const bool pos = k == 1;
-                a1 = lds_at(row, pos ? xl.own - E : xl.own + E);
-                a2 = lds_at(row, pos ? xl.own - 2 * E : xl.own + 2 * E);
-                f1 = lds_at(row, pos ? xl.own + E : xl.own - E);
+                n = lds_at(row, pos ? xl.own : xl.own + E);
+                f = (pos ? xl.edge1 : xl.edge3) ? n : lds_at(row, pos ? xl.own - E : xl.own + 2 * E);
+                o = lds_at(row, pos ? xl.own + E : xl.own);
                 w = T(1);
-                edge = pos ? xl.edge1 : xl.edge3;
+                minus = pos;
             } else {
                 const int pr = (k == 2 || k == 4) ? 0 : ((k == 5 || k == 7) ? 1 : 2);
                 const bool first = k == 2 || k == 5 || k == 6;
-                a1 = lds_at(row, first ? xl.a1[pr] : xl.f1[pr]);
-                a2 = lds_at(row, first ? xl.a2[pr] : xl.a2m[pr]);
-                f1 = lds_at(row, first ? xl.f1[pr] : xl.a1[pr]);
+                n = lds_at(row, first ? xl.a1[pr] : xl.f1[pr]);
+                f = lds_at(row, first ? xl.a2[pr] : xl.a2m[pr]);
+                o = lds_at(row, first ? xl.f1[pr] : xl.a1[pr]);
                 w = xl.ad[pr];
-                edge = first ? xl.edge_p[pr] : xl.edge_m[pr];
+                minus = first;
             }
-            a2 = edge ? T(2) * a1 - c0 : a2;
-            T o = base[k] - w * mx.apply(a2, a1, c0, f1);
-            if (moves_up(k)) o = o - my.apply(ring[S0][k], ring[S1][k], c0, ring[S3][k]);
-            if (moves_down(k)) o = o - my.apply(ring[S4][k], ring[S3][k], c0, ring[S1][k]);
-            out[k] = o;
+            const T t = mx.apply_back(n, f, o);
+            T r = minus ? base[k] - w * t : base[k] + w * t;
+            // eta term: the backward differences along the upwind direction from the ring (the row below for
+            // populations moving up, the row above for those moving down); at rows 1 and ny - 2 the far one is
+            // the near one
+            if (moves_up(k)) {
+                const T nb = c0 - ring[S1][k];
+                r = my.sub_back(r, nb, elo ? nb : ring[S1][k] - ring[S0][k], ring[S3][k] - c0);
+            }
+            if (moves_down(k)) {
+                const T nb = c0 - ring[S3][k];
+                r = my.sub_back(r, nb, ehi ? nb : ring[S3][k] - ring[S4][k], ring[S1][k] - c0);
+            }
+            out[k] = r;
         }
         wave_sync();
-    }
-
-    // Rows outside [1, ny-2] of a ring take the linear extrapolation 2 a1 - c0,
-    // which turns the second-order one-sided difference into the first-order
-    // one (the eta counterpart of the wall columns of XiLane).
-    template <int S0, int S1, int S2, int S3, int S4>
-    __device__ __forceinline__ void eta_ghosts(T (&ring)[kRing][9], bool lo, bool hi)
-    {
-        if (lo) {
-#pragma unroll
-            for (int k = 1; k < 9; ++k)
-                if (moves_up(k)) ring[S0][k] = T(2) * ring[S1][k] - ring[S2][k];
-        }
-        if (hi) {
-#pragma unroll
-            for (int k = 1; k < 9; ++k)
-                if (moves_down(k)) ring[S4][k] = T(2) * ring[S3][k] - ring[S2][k];
-        }
     }
 
     template <int R>
@@ -577,7 +493,6 @@ struct March {
         if (q >= qlo && q <= qhi) {
             T fb[9];
             if (q >= 1 && q <= ny - 2) {
-                eta_ghosts<sg(R, 4), sg(R, 3), sg(R, 2), sg(R, 1), sg(R, 0)>(gbp, q == 1, q == ny - 2);
                 const MixedWeights<T> mx(eps, sx_b * (kMetricRing ? am[sg(R, 1)] : geo[q])), my(eps, sy_b);
                 transport<sg(R, 4), sg(R, 3), sg(R, 2), sg(R, 1), sg(R, 0)>(gbp, gbp[sg(R, 2)], mx, my, q == 1, q == ny - 2, fb);
                 if (walls_b) {
@@ -623,7 +538,6 @@ struct March {
         if (do_c) {
             T hp[9], gn[9];
             double fin[S::kExactFinal ? 9 : 1];   // exact final update (FP32SRF): the FP64 sum of each population
-            eta_ghosts<sf(R, 6), sf(R, 5), sf(R, 4), sf(R, 3), sf(R, 2)>(fh, p == 1, p == ny - 2);
             const MixedWeights<T> mx(eps, sx_c * (kMetricRing ? am[sg(R, 3)] : geo[p])), my(eps, sy_c);
             if constexpr (S::kExactFinal) {
                 // f-hat(t + dt) = g + (collision increment + streaming increment): the two increments in FP32
@@ -729,7 +643,7 @@ struct March {
 };
 
 template <int PREC, bool RES, bool IMPL>
-__global__ __launch_bounds__(kWaveLanes, Tuning<PREC>::kWaves) void k_fused(StepArgs a, const StripItem* items, int w0, int nw)
+__global__ __launch_bounds__(kWaveLanes, kMarchWaves) void k_fused(StepArgs a, const StripItem* items, int w0, int nw)
 {
     const int w = w0 + (int)blockIdx.x;
     const StripItem it = items[w];
@@ -761,11 +675,8 @@ template <bool IMPL>
 hipError_t fused_prec(int prec, const StepArgs& a, const StripItem* items, int w0, int nw, bool residual, hipStream_t s)
 {
     switch (prec) {
-    case P_FP64: return fused<P_FP64, IMPL>(a, items, w0, nw, residual, s);
     case P_FP32: return fused<P_FP32, IMPL>(a, items, w0, nw, residual, s);
     case P_FP16DEV: return fused<P_FP16DEV, IMPL>(a, items, w0, nw, residual, s);
-    case P_FP32X: return fused<P_FP32X, IMPL>(a, items, w0, nw, residual, s);
-    case P_FP32SR: return fused<P_FP32SR, IMPL>(a, items, w0, nw, residual, s);
     case P_FP32SRF: return fused<P_FP32SRF, IMPL>(a, items, w0, nw, residual, s);
     }
     return hipErrorInvalidValue;
