@@ -89,15 +89,15 @@ __device__ __forceinline__ void residual_add(const T (&gn)[9], const T (&old)[3]
     moments(gn, P, ux, uy);
     const double du = (double)ux - (double)old[1], dv = (double)uy - (double)old[2], dp = (double)P - (double)old[0];
     const double sd = dp - ref[0], sp = (double)P - ref[1];
-    acc[0] += du * du + dv * dv;
-    acc[1] += (double)ux * ux + (double)uy * uy;
-    acc[2] += dp * dp;
-    acc[3] += (double)P * P;
+    acc[0] = fused(du, du, fused(dv, dv, acc[0]));
+    acc[1] = fused((double)ux, (double)ux, fused((double)uy, (double)uy, acc[1]));
+    acc[2] = fused(dp, dp, acc[2]);
+    acc[3] = fused((double)P, (double)P, acc[3]);
     acc[4] += sd;
     acc[5] += sp;
     acc[6] += (isfinite((double)ux) && isfinite((double)uy) && isfinite((double)P)) ? 0.0 : 1.0;
-    acc[7] += sd * sd;
-    acc[8] += sp * sp;
+    acc[7] = fused(sd, sd, acc[7]);
+    acc[8] = fused(sp, sp, acc[8]);
 }
 
 // Sums of the residual terms over the wavefront, in a fixed order: lane q < kPartials returns sum q.  Eight of the nine

@@ -159,8 +159,10 @@ __device__ __forceinline__ T lds_at(const T* row, uint32_t byte_offset)
 }
 
 // LDS of one wavefront.  NG is 9 where stage C reads the stored row again
-// (exact final update), else 0.
-template <typename T, int NG>
+// (exact final update), else 0.  NM is 3 where stage A keeps the old moments of
+// the row for the residual sums of stage C (the exact final update forms them
+// from the stored row it reads), else 0.
+template <typename T, int NG, int NM>
 struct WaveLds {
     T xs[xs_rows(NG != 0)][kRowLds];  // one row of each moving population of a pass, for the xi stencils
     T hp[kRing][9][kWaveLanes];       // f-hat+ of rows t-4 .. t (lane-private); the slot of row ny keeps
@@ -170,7 +172,10 @@ struct WaveLds {
     T gr[NG ? kRing : 0][kGxRing][kWaveLanes];   // stored f-hat of populations 0 .. kGxRing - 1, rows t-4 .. t
     T gx[NG ? 9 - kGxRing : 0][kWaveLanes];      // stored f-hat of the other populations of the stage-C row,
                                                  // written by the buffer unit
+    T om[NM ? kRing : 0][NM][kWaveLanes];        // P, u, v of rows t-4 .. t (lane-private)
 };
+template <int PREC, bool RES>
+using LdsOf = WaveLds<typename Storage<PREC>::T, Storage<PREC>::kExactFinal ? 9 : 0, RES && !Storage<PREC>::kExactFinal ? 3 : 0>;
 
 // Compiler-level memory barrier: no memory operation is moved across it, and
 // it emits no instruction.
@@ -227,7 +232,7 @@ struct March {
     const StepArgs& a;
     const StripItem& it;
     const CavityDesc& c;
-    WaveLds<T, S::kExactFinal ? 9 : 0>& sh;
+    LdsOf<PREC, RES>& sh;
     double (&acc)[kPartials];
     double ref[2];         // shifts of the residual sums (RES)
 
@@ -257,7 +262,7 @@ struct March {
     L ln_;
 
     __device__ __forceinline__ March(const StepArgs& a_, const StripItem& it_, const CavityDesc& c_,
-                                     WaveLds<T, S::kExactFinal ? 9 : 0>& sh_,
+                                     LdsOf<PREC, RES>& sh_,
                                      double (&acc_)[kPartials])
         : a(a_), it(it_), c(c_), sh(sh_), acc(acc_), ref{0.0, 0.0}, pl(c_),
           xl(threadIdx.x, it_.i0 - kHaloCols + (int)threadIdx.x, c_.nx,
@@ -480,6 +485,12 @@ struct March {
                     if (k < kGxRing) sh.gr[hs][k][lane] = g[k];
                 }
             }
+            if constexpr (RES && !S::kExactFinal) {
+                T m[3];
+                moments(g, m[0], m[1], m[2]);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) sh.om[hs][k][lane] = m[k];
+            }
             lam[sg(R, 0)] = l;
             Buf<L>::st(L(l), rl_out, out_col && t >= j0 && t < j1 ? loff(t) : kDroppedOffset, 0u);
         } else if constexpr (S::kExactFinal) {
@@ -538,6 +549,7 @@ struct March {
         if (do_c) {
             T hp[9], gn[9];
             double fin[S::kExactFinal ? 9 : 1];   // exact final update (FP32SRF): the FP64 sum of each population
+            T old[3];                             // RES: old moments of the row
             const MixedWeights<T> mx(eps, sx_c * (kMetricRing ? am[sg(R, 3)] : geo[p])), my(eps, sy_c);
             if constexpr (S::kExactFinal) {
                 // f-hat(t + dt) = g + (collision increment + streaming increment): the two increments in FP32
@@ -550,11 +562,15 @@ struct March {
                     wait_vm<10>();   // the LDS copies of row p were followed by the ten loads of row t + 1
                 else
                     wait_vm<0>();
+                T g[9];
 #pragma unroll
                 for (int k = 0; k < 9; ++k) {
-                    const T g = k < kGxRing ? sh.gr[hs][k][lane] : sh.gx[k - kGxRing][lane];
-                    fin[k] = (double)S::cvt(g, k) + (double)gn[k];
+                    g[k] = S::cvt(k < kGxRing ? sh.gr[hs][k][lane] : sh.gx[k - kGxRing][lane], k);
+                    fin[k] = (double)g[k] + (double)gn[k];
                 }
+                // old moments of a residual step from the row that is here: with the row read from memory once more
+                // for them a residual step of 64 x 513^2 took 690 us, so 618 (FP32, moments kept by stage A: 573 -> 500)
+                if (RES) moments(g, old[0], old[1], old[2]);
                 if (RES || walls_c || (p == 1 && j0 == 0) || (p == ny - 2 && j1 == ny)) {
 #pragma unroll
                     for (int k = 0; k < 9; ++k) gn[k] = T(fin[k]);
@@ -585,8 +601,11 @@ struct March {
             else
                 encode_row(p, gn, enc);
             if (RES && out_col) {
-                T old[3];
-                old_moments(p, old);
+                if constexpr (!S::kExactFinal) {
+                    const int hs = hslot(p);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) old[k] = sh.om[hs][k][lane];
+                }
                 residual_add(gn, old, ref, acc);
             }
             if (p == 1 && j0 == 0) {   // bottom wall row from row 1
@@ -649,7 +668,7 @@ __global__ __launch_bounds__(kWaveLanes, kMarchWaves) void k_fused(StepArgs a, c
     const StripItem it = items[w];
     if (it.unit < 0) return;   // padding of a per-XCD queue
     const CavityDesc c = a.desc[it.cav];
-    __shared__ WaveLds<typename Storage<PREC>::T, Storage<PREC>::kExactFinal ? 9 : 0> sh;
+    __shared__ LdsOf<PREC, RES> sh;
     double acc[kPartials];
 #pragma unroll
     for (int q = 0; q < kPartials; ++q) acc[q] = 0.0;

@@ -1,6 +1,6 @@
 // step_tile.hip -- one launch per IFDLBM time step (arXiv:2306.07603,
-// Section 4, Steps (2)-(6)) for batches too small to fill the GPU with the
-// row march of step_fused.hip: one node per thread.
+// Section 4, Steps (2)-(6)) for batches too small to fill the GPU with the row
+// march (step_fused.hip, step_block.hip): one node per thread.
 //
 // Work item: a tile of output columns [i0, i1) and rows [j0, j1) of one
 // cavity, at most (LX - 8) x (LY - 8) nodes.  The workgroup holds the nodes
@@ -15,12 +15,12 @@
 //                          (Step 6), store, residual sums of Eq. (2.19)
 // What bounds it: for one small cavity the chain of one step, about 900
 // instructions of one wavefront behind two dependent loads (5.2 us per step
-// of a 33 x 33 FP32SRF cavity and 5.7 us in FP64, against 35.0 and 43.4 us of
-// the march, whose items are chains of at least 16 rows); from about 256 x 256
+// of a 33 x 33 FP32SRF cavity and 5.7 us in FP64, against 35.0 us of the FP32
+// march, whose items are chains of at least 16 rows); from about 256 x 256
 // nodes on the issue of vector instructions (78 % of the peak on 64 x 513^2 in
 // FP32SRF, shape 2).  The halo is recomputed: a 24 x 24 tile runs stage A on
-// 1.8 and stage B on 1.4 times its nodes, so past a few million nodes the march
-// with its 1.3 wins (choose_kernel in api.hip holds the measured line).
+// 1.8 and stage B on 1.4 times its nodes, so past a few million nodes (in FP64
+// half a million) the march with its 1.3 wins (choose_kernel in api.hip holds the measured line).
 //
 // Every node is rounded as the march rounds it (the same stage functions and
 // the same order in the stencils), so which of the two runs never shows in
