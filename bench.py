@@ -53,8 +53,9 @@ def log(msg: str) -> None:
 
 # Kernel sources whose content the measured traffic belongs to: the traffic
 # record in profiles/ is used only while these files and the compiler flags
-# of step_fused.hip are unchanged.
-KERNEL_SOURCES = ["paper_2306_07603_amd/csrc/step_fused.hip", "paper_2306_07603_amd/csrc/lbm_device.h",
+# of step_fused.hip (FP32 arithmetic) and step_block.hip (FP64) are unchanged.
+KERNEL_SOURCES = ["paper_2306_07603_amd/csrc/step_fused.hip", "paper_2306_07603_amd/csrc/step_block.hip",
+                  "paper_2306_07603_amd/csrc/step_common.h", "paper_2306_07603_amd/csrc/lbm_device.h",
                   "paper_2306_07603_amd/csrc/ifdlbm_internal.h"]
 TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "k_fused_traffic_batch256.txt")
 
@@ -63,7 +64,8 @@ def kernel_source_digest() -> str:
     import hashlib
     from paper_2306_07603_amd import _build
     h = hashlib.sha256()
-    h.update(repr(_build.FILE_FLAGS.get("step_fused.hip", [])).encode())
+    for name in ("step_fused.hip", "step_block.hip"):
+        h.update(repr(_build.FILE_FLAGS.get(name, [])).encode())
     for rel in KERNEL_SOURCES:
         with open(os.path.join(ROOT, rel), "rb") as f:
             h.update(f.read())
