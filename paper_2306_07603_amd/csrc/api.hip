@@ -113,7 +113,7 @@ struct ifdlbm_s {
     std::vector<StripItem> act_sorted;     // the same items, longest first (batched launch)
     StripItem* d_act_sorted = nullptr;
     std::vector<int> cav_shape;            // kernel of each cavity's items: a tile shape, or kMarch
-    size_t units_alloc = 0, items_alloc = 0, sorted_alloc = 0;   // entries of d_partial and of the item lists
+    size_t max_units = 0;                  // entries of d_partial, d_act_items and (times kXcds) d_act_sorted
     std::vector<int32_t> unit_first, unit_count;   // per cavity, in the active unit list
     int32_t *d_unit_first = nullptr, *d_unit_count = nullptr;
     double* d_partial = nullptr;
@@ -154,22 +154,8 @@ int dalloc(P** p, size_t bytes)
     return IFDLBM_OK;
 }
 
-// Device array of at least n entries (n_alloc: the entries it has); its contents are not kept.
-template <typename P>
-int grow(P** p, size_t& n_alloc, size_t n, size_t entry)
-{
-    if (n <= n_alloc) return IFDLBM_OK;
-    if (*p) IFD_HIP(hipFree(*p));
-    *p = nullptr;
-    n_alloc = 0;
-    const int rc = dalloc(p, n * entry);
-    if (!rc) n_alloc = n;
-    return rc;
-}
-
 int units_per_step(const ifdlbm_s* h) { return h->opt.kernel == IFDLBM_KERNEL_STAGED ? 5 : 1; }
 
-// Rebuild the unit lists of the running cavities (after creation, retirement or restore).
 // First row of segment g of ng over ny rows: the even split, moved to the
 // nearest row that is 4 (mod 5).  The fused kernel's march then starts at a
 // row that is 0 (mod 5), so every row is computed by the same unrolled copy
@@ -248,6 +234,7 @@ BlockPlan plan_block(const ifdlbm_s* h, int one_cav)
 // 4.5 .. 5.3 us at these sizes.  Which of them is least follows the grids, not the node count alone (a strip of a 65
 // wide cavity uses 33 of its 64 lanes), so the three are compared.
 constexpr int kMarch = -1;
+constexpr int64_t kShape1Tiles2 = 6 * kCus;   // FP64: tiles of shape 2 up to which shape 1 is considered
 
 int choose_kernel(const ifdlbm_s* h, int one_cav = -1)
 {
@@ -263,7 +250,7 @@ int choose_kernel(const ifdlbm_s* h, int one_cav = -1)
     if (tiles[1] <= 2 * kCus) return 1;
     const int prec = h->opt.precision;
     if (t_elem_size(prec) == 8) {
-        const int shape = tiles[2] > kCus && tiles[2] < 6 * kCus ? 1 : 2;
+        const int shape = tiles[2] > kCus && tiles[2] < kShape1Tiles2 ? 1 : 2;
         const double tile = shape == 1 ? 6.9 * (double)tiles[1] / (2 * kCus) : 10.1 * (double)tiles[2] / kCus;
         return 4.8 * plan_block(h, one_cav).cost < tile ? kMarch : shape;
     }
@@ -287,6 +274,32 @@ int segment_rows(const ifdlbm_s* h, int one_cav = -1)
         if (n >= (size_t)kTargetItems) return seg;
     }
     return kSegCandidates[sizeof(kSegCandidates) / sizeof(kSegCandidates[0]) - 1];
+}
+
+// Work items that any choice of kernel and segment length gives any of the handle's cavities running: create reserves
+// the lists for them, so that a later choice (retirement, restore, autotuner) allocates nothing and cannot fail for
+// want of memory.  A march has at most its shortest segments; shapes 0 and 1 are only chosen up to a number of tiles,
+// for shape 1 in FP64 through that of shape 2, of whose tiles one holds at most three of shape 1.
+size_t max_items(const ifdlbm_s* h)
+{
+    constexpr int kShortest = kSegCandidates[sizeof(kSegCandidates) / sizeof(kSegCandidates[0]) - 1];
+    static_assert(kTileCols[1] == kTileCols[2] && 3 * kTileRows[1] >= kTileRows[2], "tiles of shape 1 in one of shape 2");
+    const size_t most0 = 2 * kCus, most1 = t_elem_size(h->opt.precision) == 8 ? 3 * kShape1Tiles2 : 2 * kCus;
+    auto largest = [&](size_t march, const size_t(&tiles)[kTileShapes]) {
+        return std::max(std::max(march, tiles[2]), std::max(std::min(tiles[0], most0), std::min(tiles[1], most1)));
+    };
+    size_t march = 0, tiles[kTileShapes] = {}, alone = 0;
+    for (const CavityDesc& d : h->desc) {
+        const size_t m = (size_t)ceil_div(d.ny, kShortest) * ceil_div(d.nx, kStripOut);
+        size_t t[kTileShapes];
+        for (int s = 0; s < kTileShapes; ++s) {
+            t[s] = (size_t)ceil_div(d.nx, kTileCols[s]) * ceil_div(d.ny, kTileRows[s]);
+            tiles[s] += t[s];
+        }
+        march += m;
+        alone += largest(m, t);
+    }
+    return h->opt.batched ? largest(march, tiles) : alone;
 }
 
 // Order of the items in the batched launch.  Workgroup w of a launch goes to
@@ -330,8 +343,10 @@ void order_for_batch(ifdlbm_s* h)
         for (int x = 0; x < kXcds; ++x) h->act_sorted.push_back(r < queue[x].size() ? queue[x][r] : empty);
 }
 
+// Rebuild the unit lists of the running cavities (after creation, retirement or restore).
 int rebuild_worklists(ifdlbm_s* h)
 {
+    h->graph_dirty = true;   // a captured graph holds the old lists
     h->act_blocks.clear();
     h->act_items.clear();
     const int seg_batch = segment_rows(h), shape_batch = choose_kernel(h);
@@ -367,15 +382,12 @@ int rebuild_worklists(ifdlbm_s* h)
         }
     }
     order_for_batch(h);
-    // the lists grow with the item count of the chosen kernel; nothing of the old ones is kept
-    int rc = IFDLBM_OK;
-    const size_t units = h->opt.kernel == IFDLBM_KERNEL_STAGED ? h->act_blocks.size() : h->act_items.size();
-    if (units > h->units_alloc || h->act_items.size() > h->items_alloc || h->act_sorted.size() > h->sorted_alloc)
-        IFD_HIP(hipStreamSynchronize(h->stream));
-    rc = grow(&h->d_partial, h->units_alloc, units, kPartials * sizeof(double));
-    if (!rc) rc = grow(&h->d_act_items, h->items_alloc, h->act_items.size(), sizeof(StripItem));
-    if (!rc) rc = grow(&h->d_act_sorted, h->sorted_alloc, h->act_sorted.size(), sizeof(StripItem));
-    if (rc) return rc;
+    if (h->act_items.size() > h->max_units || h->act_sorted.size() > h->max_units * kXcds) {
+        h->act_items.clear();
+        h->act_sorted.clear();
+        h->unit_count.assign(h->n_cav, 0);
+        return fail(IFDLBM_EDEVICE, "work lists larger than those reserved at creation");
+    }
     if (!h->act_blocks.empty())
         IFD_HIP(hipMemcpyAsync(h->d_act_blocks, h->act_blocks.data(), h->act_blocks.size() * sizeof(NodeBlock),
                                hipMemcpyHostToDevice, h->stream));
@@ -390,7 +402,6 @@ int rebuild_worklists(ifdlbm_s* h)
     IFD_HIP(hipMemcpyAsync(h->d_desc, h->desc.data(), h->n_cav * sizeof(CavityDesc), hipMemcpyHostToDevice, h->stream));
     // the host vectors may change before the copies run
     IFD_HIP(hipStreamSynchronize(h->stream));
-    h->graph_dirty = true;
     return IFDLBM_OK;
 }
 
@@ -803,6 +814,11 @@ static int ifdlbm_create_impl(const ifdlbm_cavity* cav, int32_t n_cav, const ifd
     }
     if (!rc) rc = dalloc(&h->d_all_blocks, h->all_blocks.size() * sizeof(NodeBlock));
     if (!rc) rc = dalloc(&h->d_act_blocks, n_blocks * sizeof(NodeBlock));
+    h->max_units = o.kernel == IFDLBM_KERNEL_STAGED ? 0 : max_items(h);
+    if (!rc) rc = dalloc(&h->d_act_items, h->max_units * sizeof(StripItem));
+    // per-XCD queues are padded to equal length: at most kXcds entries per item
+    if (!rc) rc = dalloc(&h->d_act_sorted, h->max_units * kXcds * sizeof(StripItem));
+    if (!rc) rc = dalloc(&h->d_partial, (o.kernel == IFDLBM_KERNEL_STAGED ? n_blocks : h->max_units) * kPartials * sizeof(double));
     if (!rc) rc = dalloc(&h->d_unit_first, n_cav * sizeof(int32_t));
     if (!rc) rc = dalloc(&h->d_unit_count, n_cav * sizeof(int32_t));
     if (!rc) rc = dalloc(&h->d_res, (size_t)n_cav * kResult * sizeof(double));

@@ -1,0 +1,132 @@
+"""The host side of the library against a stand-in for the GPU in host memory
+(host_device.hip): the work lists of a handle as its cavities retire and come
+back, with device memory exhausted after creation.  Every launch, and every
+launch of a replayed graph, is checked against the live allocations."""
+import ctypes
+import os
+import random
+import subprocess
+
+import numpy as np
+import pytest
+
+import paper_2306_07603_amd as M
+from paper_2306_07603_amd import _build
+
+PRECISIONS = ["fp64", "fp32", "fp16dev", "fp32x", "fp32sr", "fp32srf"]
+TOL = 1e-6
+
+
+class Host:
+    """api.hip on the stand-in: the C ABI, called as the binding calls it."""
+
+    def __init__(self, path):
+        self.L = L = ctypes.CDLL(path)
+        L.ifdlbm_create.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p, ctypes.POINTER(ctypes.c_void_p)]
+        L.ifdlbm_step.argtypes = [ctypes.c_void_p, ctypes.c_int64]
+        L.ifdlbm_run_to_steady.argtypes = [ctypes.c_void_p, ctypes.c_double, ctypes.c_int64] + [ctypes.c_void_p] * 3
+        L.ifdlbm_get_residuals.argtypes = [ctypes.c_void_p] * 3
+        L.ifdlbm_set_state.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p]
+        L.ifdlbm_destroy.argtypes = [ctypes.c_void_p]
+        L.ifdlbm_destroy.restype = None
+        L.host_reset.argtypes = [ctypes.c_long, ctypes.c_long]
+        L.host_reset.restype = None
+        L.host_converge.argtypes = [ctypes.c_void_p, ctypes.c_int]
+        L.host_converge.restype = None
+
+    def create(self, sizes, **opt):
+        self.L.host_reset(-1, -1)
+        self.sizes = sizes
+        arr = (M.ifdlbm.ifdlbm_cavity * len(sizes))(*[M.Cavity(a, b, 400.0, 0.8, 60.0).c() for a, b in sizes])
+        o = M.ifdlbm_default_options(**opt)
+        h = ctypes.c_void_p()
+        assert self.L.ifdlbm_create(arr, len(sizes), ctypes.byref(o), ctypes.byref(h)) == 0
+        return h
+
+    def exhaust(self):
+        """No device allocation succeeds from here on."""
+        self.L.host_reset(0, -1)
+
+    def converge(self, flags):
+        a = np.ascontiguousarray(flags, dtype=np.int32)
+        self.L.host_converge(a.ctypes.data, a.size)
+
+    def restart(self, h, c):
+        nx, ny = self.sizes[c]
+        F, lam = np.zeros((9, ny, nx)), np.ones((ny, nx))
+        return self.L.ifdlbm_set_state(h, c, F.ctypes.data, lam.ctypes.data)
+
+    def faults(self):
+        text = ctypes.create_string_buffer(200)
+        n = self.L.host_faults(text, 200)
+        return n, text.value.decode()
+
+    def last_kernel(self):
+        text = ctypes.create_string_buffer(20)
+        self.L.host_last_kernel(text, 20)
+        return text.value.decode()
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    d = tmp_path_factory.mktemp("host")
+    objs = []
+    for src in (os.path.join(_build.CSRC, "api.hip"), os.path.join(os.path.dirname(__file__), "host_device.hip")):
+        objs.append(str(d / (os.path.basename(src) + ".o")))
+        subprocess.run([_build.HIPCC, "--offload-host-only", "-x", "hip", "-O1", "-std=c++17", "-fPIC", "-I", _build.INCLUDE,
+                        "-I", _build.CSRC, '-DIFD_SOURCE_DIGEST="host"', "-c", src, "-o", objs[-1]], check=True)
+    lib = str(d / "libhost.so")
+    # the stand-in's runtime, also where the process has loaded the GPU's
+    subprocess.run(["g++", "-shared", "-fPIC", "-Wl,-Bsymbolic", "-o", lib, *objs], check=True)
+    return Host(lib)
+
+
+# (batch, cavities left, kernel before, kernel after): the tiles of those left are more items than the march of all
+RETIRE = [("fp32srf", 64, 15, (513, 513), "march", "tile"), ("fp64", 40, 10, (129, 129), "block", "tile")]
+
+
+@pytest.mark.parametrize("case", RETIRE, ids=lambda c: c[0])
+@pytest.mark.parametrize("graph", [0, 4])
+def test_retirement_needs_no_memory(host, case, graph):
+    precision, n, left, size, before, after = case
+    h = host.create([size] * n, precision=precision, graph_steps=graph, residual_every=2)
+    host.exhaust()
+    host.converge([0] * n)
+    assert host.L.ifdlbm_step(h, 8) == 0 and host.last_kernel() == before
+    host.converge([0] * left + [1] * (n - left))
+    assert host.L.ifdlbm_run_to_steady(h, TOL, 2, None, None, None) == M.IFDLBM_ENOTCONVERGED
+    assert host.L.ifdlbm_step(h, 9) == 0 and host.last_kernel() == after
+    assert host.faults() == (0, "")
+    # and back: every cavity restarted
+    for c in range(left, n):
+        assert host.restart(h, c) == 0
+    assert host.L.ifdlbm_step(h, 9) == 0 and host.last_kernel() == before
+    assert host.faults() == (0, "")
+    host.L.ifdlbm_destroy(h)
+
+
+@pytest.mark.parametrize("batched", [1, 0])
+@pytest.mark.parametrize("precision", PRECISIONS)
+def test_lists_hold_any_running_set(host, precision, batched):
+    """Batches of every size class, with random sets of cavities stopped and restarted."""
+    rng = random.Random(7)
+    for trial in range(12):
+        count = rng.choice((1, 2, 7, 30, 120))
+        side = rng.choice((5, 9, 25, 60, 130, 300, 700)) if count < 100 else rng.choice((5, 25, 60, 130))
+        sizes = [(max(5, int(side * rng.uniform(0.4, 2.0))), max(5, int(side * rng.uniform(0.4, 2.0)))) for _ in range(count)]
+        h = host.create(sizes, precision=precision, batched=batched, residual_every=1)
+        host.exhaust()
+        stopped = []
+        for _ in range(4):
+            flags = [int(rng.random() < 0.6) for _ in range(count)]
+            host.converge(flags)
+            rc = host.L.ifdlbm_run_to_steady(h, TOL, 1, None, None, None)
+            assert rc in (M.IFDLBM_OK, M.IFDLBM_ENOTCONVERGED), (trial, rc)
+            stopped = sorted(set(stopped) | {c for c in range(count) if flags[c]})
+            host.converge([0] * count)
+            assert host.L.ifdlbm_step(h, 2) == 0
+            assert host.faults() == (0, ""), (trial, sizes[:3], count)
+            for c in rng.sample(stopped, len(stopped) // 2):
+                assert host.restart(h, c) == 0
+                stopped.remove(c)
+        host.L.ifdlbm_destroy(h)
