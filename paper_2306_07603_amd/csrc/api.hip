@@ -1117,8 +1117,10 @@ static int ifdlbm_autotune_impl(ifdlbm_t* h, int32_t steps_per_trial, int32_t* s
         if (seg <= max_ny || seg == kSegCandidates[sizeof(kSegCandidates) / sizeof(kSegCandidates[0]) - 1]) trials.push_back(seg);
     h->opt.segment_rows = 0;
     const int tile = choose_kernel(h);
-    // the automatic kernel, where it is not one of the trials already
-    if ((tile != kMarch || t_elem_size(prec) == 8) && h->opt.batched) trials.push_back(0);
+    // the automatic choice, where it is not one of the trials already: for launches per cavity a kernel for each
+    const bool among = h->opt.batched && tile == kMarch && t_elem_size(prec) == 4 &&
+                       std::find(trials.begin(), trials.end(), ::segment_rows(h)) != trials.end();
+    if (!among) trials.push_back(0);
     const int auto_rows = tile == kMarch ? plan_block(h, -1).rows : kTileRows[tile];
     for (int32_t seg : trials) {
         if (rc) break;

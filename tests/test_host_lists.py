@@ -1,7 +1,8 @@
 """The host side of the library against a stand-in for the GPU in host memory
 (host_device.hip): the work lists of a handle as its cavities retire and come
-back, with device memory exhausted after creation.  Every launch, and every
-launch of a replayed graph, is checked against the live allocations."""
+back, with device memory exhausted after creation, and what the autotuner
+keeps.  Every launch, and every launch of a replayed graph, is checked against
+the live allocations."""
 import ctypes
 import os
 import random
@@ -27,6 +28,8 @@ class Host:
         L.ifdlbm_run_to_steady.argtypes = [ctypes.c_void_p, ctypes.c_double, ctypes.c_int64] + [ctypes.c_void_p] * 3
         L.ifdlbm_get_residuals.argtypes = [ctypes.c_void_p] * 3
         L.ifdlbm_set_state.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p]
+        L.ifdlbm_autotune.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32),
+                                      ctypes.POINTER(ctypes.c_double)]
         L.ifdlbm_destroy.argtypes = [ctypes.c_void_p]
         L.ifdlbm_destroy.restype = None
         L.host_reset.argtypes = [ctypes.c_long, ctypes.c_long]
@@ -130,3 +133,16 @@ def test_lists_hold_any_running_set(host, precision, batched):
                 assert host.restart(h, c) == 0
                 stopped.remove(c)
         host.L.ifdlbm_destroy(h)
+
+
+@pytest.mark.parametrize("batched", [1, 0])
+@pytest.mark.parametrize("precision", PRECISIONS)
+def test_autotune_keeps_a_faster_automatic_choice(host, precision, batched):
+    """Small cavities, on a stand-in whose tiles are faster than any march: the tuned handle steps on tiles, as the
+    untuned one does, in one launch or one per cavity."""
+    h = host.create([(33, 33), (65, 49)], precision=precision, batched=batched)
+    rows = ctypes.c_int32()
+    assert host.L.ifdlbm_autotune(h, 3, ctypes.byref(rows), None) == 0
+    assert host.L.ifdlbm_step(h, 1) == 0 and host.last_kernel() == "tile"
+    assert host.faults() == (0, "")
+    host.L.ifdlbm_destroy(h)
