@@ -95,6 +95,13 @@ def measured_record(precision: str, what: str, segment_rows):
     return float(rec[key]) if key in rec else None
 
 
+def march_rows(specs, rows: int, work_items: int):
+    """rows where the handle steps by the row march at that segment length (its work items are then the strips of at
+    most 56 columns times the segments), else None: another kernel, which the counter record does not hold."""
+    items = sum(-(-s.n_xi // 56) * -(-s.n_eta // rows) for s in specs) if rows else 0
+    return rows if items == work_items else None
+
+
 def binding_limit(hbm_frac: float, valu):
     """The limit the kernel runs into: "valu" when the VALU issue fraction of the
     same launches exceeds the memory fraction `hbm_frac`, else "hbm"; None
@@ -286,8 +293,9 @@ def main() -> int:
     h = M.ifdlbm_create(cav, opt)
     seg_rows = args.segment_rows or None
     if args.autotune_steps > 0 and not args.segment_rows and args.kernel == "fused":
-        seg_rows, tuned_ms = M.ifdlbm_autotune(h, args.autotune_steps)
-        log("autotune: %d-row segments, %.3f ms/step in its trials" % (seg_rows, tuned_ms))
+        rows, tuned_ms = M.ifdlbm_autotune(h, args.autotune_steps)
+        seg_rows = march_rows(specs, rows, M.ifdlbm_info(h)["work_items"])
+        log("autotune: %s, %.3f ms/step in its trials" % ("%d-row segments" % seg_rows if seg_rows else "tiles", tuned_ms))
     info = M.ifdlbm_info(h)
     log("created %d cavities, %d nodes per step, %d work items" % (info["n_cavities"], info["nodes"], info["work_items"]))
     ex = executed(warmup_run, args.steps, graph_steps, residual_every)   # the autotuner restores the step count

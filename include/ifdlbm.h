@@ -223,12 +223,13 @@ int ifdlbm_status(ifdlbm_t* h, int32_t cav);
 
 /* Tile-shape autotuner of the fused kernel: times steps_per_trial steps (after one warm-up step) of the
    handle's running cavities for every candidate row-segment length (8 ... 128 rows) and for the automatic choice
-   where that is another one (a tile, or another segment length of the FP64 march), keeps the fastest, and restores
-   the state, step count, residual sums and random-word counter, so later results are those
-   without the call (they do not depend on the segmentation).  *segment_rows and *ms_per_step (either may be
-   NULL) receive the choice (rows per segment or of the tile) and its time per step; 0 for the staged schedule, which
-   has no tile shape.  Device memory for one copy of the state is allocated and freed inside the call, which
-   synchronises the stream.
+   where that is another one (tiles, another segment length of the FP64 march, a kernel for each cavity with a launch
+   per cavity), keeps the fastest, and restores the state, step count, residual sums and random-word counter, so later
+   results are those without the call (they do not depend on the segmentation).  *segment_rows and *ms_per_step (either
+   may be NULL) receive the segment length of the fastest march, a value for options.segment_rows of another handle, and
+   the time per step of what is kept; where that is not a march, another handle takes it with segment_rows 0.  Both are
+   0 for the staged schedule, which has no tile shape.  Device memory for one copy of the state is allocated and freed
+   inside the call, which synchronises the stream.
    Errors: EINVAL (steps_per_trial outside [1, 10000]), ENOMEM, EDEVICE. */
 int ifdlbm_autotune(ifdlbm_t* h, int32_t steps_per_trial, int32_t* segment_rows, double* ms_per_step);
 

@@ -1105,9 +1105,8 @@ static int ifdlbm_autotune_impl(ifdlbm_t* h, int32_t steps_per_trial, int32_t* s
         return e;
     };
     if (!rc && save() != hipSuccess) rc = fail(IFDLBM_EDEVICE, "autotune: state backup");
-    int best = 0;       // rows per item of the fastest kernel, and the option that selects it (0: the automatic choice)
-    int32_t best_opt = rows0;
-    float best_ms = 0.0f;
+    int32_t best = -1, best_rows = 0;   // the fastest option (0: the automatic choice), and the fastest forced length
+    float best_ms = 0.0f, best_rows_ms = 0.0f;
     const int rec_every = h->rec_every;
     h->rec_every = 0;   // trials take no probe samples
     int max_ny = 0;
@@ -1121,7 +1120,8 @@ static int ifdlbm_autotune_impl(ifdlbm_t* h, int32_t steps_per_trial, int32_t* s
     const bool among = h->opt.batched && tile == kMarch && t_elem_size(prec) == 4 &&
                        std::find(trials.begin(), trials.end(), ::segment_rows(h)) != trials.end();
     if (!among) trials.push_back(0);
-    const int auto_rows = tile == kMarch ? plan_block(h, -1).rows : kTileRows[tile];
+    const bool planned = h->opt.batched && tile == kMarch && t_elem_size(prec) == 8;   // a length the march can be given
+    const int32_t planned_rows = planned ? plan_block(h, -1).rows : 0;
     for (int32_t seg : trials) {
         if (rc) break;
         h->opt.segment_rows = seg;
@@ -1133,15 +1133,19 @@ static int ifdlbm_autotune_impl(ifdlbm_t* h, int32_t steps_per_trial, int32_t* s
         if (!rc && hipEventSynchronize(e1) != hipSuccess) rc = fail(IFDLBM_EDEVICE, "hipEventSynchronize");
         float ms = 0.0f;
         if (!rc && hipEventElapsedTime(&ms, e0, e1) != hipSuccess) rc = fail(IFDLBM_EDEVICE, "hipEventElapsedTime");
-        if (!rc && (best == 0 || ms < best_ms)) {
-            best = seg ? seg : auto_rows;
-            best_opt = seg;
+        if (!rc && (best < 0 || ms < best_ms)) {
+            best = seg;
             best_ms = ms;
+        }
+        const int32_t rows = seg ? seg : planned_rows;
+        if (!rc && rows && (best_rows == 0 || ms < best_rows_ms)) {
+            best_rows = rows;
+            best_rows_ms = ms;
         }
         if (!rc && restore() != hipSuccess) rc = fail(IFDLBM_EDEVICE, "autotune: state restore");
     }
     h->rec_every = rec_every;
-    h->opt.segment_rows = rc ? rows0 : best_opt;
+    h->opt.segment_rows = rc ? rows0 : best;
     int rc2 = rebuild_worklists(h);
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
@@ -1150,7 +1154,7 @@ static int ifdlbm_autotune_impl(ifdlbm_t* h, int32_t steps_per_trial, int32_t* s
         if (p) (void)hipFree(p);
     if (rc) return rc;
     if (rc2) return rc2;
-    if (segment_rows) *segment_rows = best;
+    if (segment_rows) *segment_rows = best_rows;
     if (ms_per_step) *ms_per_step = best_ms / steps_per_trial;
     return IFDLBM_OK;
 }

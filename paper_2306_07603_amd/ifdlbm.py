@@ -369,7 +369,7 @@ def ifdlbm_adjoint(cavity: Cavity, options: Optional[ifdlbm_options] = None, n_s
 
 
 def ifdlbm_autotune(h: Handle, steps_per_trial: int = 20):
-    """(segment rows chosen, ms per step) of the fused kernel's tile-shape autotuner."""
+    """(segment rows of the fastest march, ms per step of what is kept) of the fused kernel's tile-shape autotuner."""
     rows, ms = ctypes.c_int32(0), ctypes.c_double(0.0)
     _check(lib().ifdlbm_autotune(h.ptr, steps_per_trial, ctypes.byref(rows), ctypes.byref(ms)))
     return rows.value, ms.value

@@ -51,6 +51,18 @@ def test_counter_record_covers_the_autotuner_choices():
                 assert float(rec["%s_per_launch_%s_seg%d" % (what, prec, seg)]) > 0, (what, prec, seg)
 
 
+def test_a_tile_run_is_not_taken_for_a_march():
+    """The rows the autotuner reports name a march: the bench records them only where the handle steps by it."""
+    sys.path.insert(0, ROOT)
+    import bench
+    from paper_2306_07603_amd.workloads import CavitySpec
+    specs = [CavitySpec(129, 97, 100.0, 0.8, 60.0), CavitySpec(57, 33, 100.0, 0.8, 60.0)]
+    march, tiles = 3 * 3 + 2 * 1, 17 * 13 + 8 * 5
+    assert bench.march_rows(specs, 40, march) == 40
+    assert bench.march_rows(specs, 40, tiles) is None
+    assert bench.march_rows(specs, 0, march) is None
+
+
 def test_timed_schedule_and_what_it_runs():
     """The timed region of the default run is whole graph replays each with one residual step; with fewer
     timed steps than a graph holds, the graph and the residual interval shrink to the timed count and the

@@ -138,11 +138,18 @@ def test_lists_hold_any_running_set(host, precision, batched):
 @pytest.mark.parametrize("batched", [1, 0])
 @pytest.mark.parametrize("precision", PRECISIONS)
 def test_autotune_keeps_a_faster_automatic_choice(host, precision, batched):
-    """Small cavities, on a stand-in whose tiles are faster than any march: the tuned handle steps on tiles, as the
-    untuned one does, in one launch or one per cavity."""
-    h = host.create([(33, 33), (65, 49)], precision=precision, batched=batched)
-    rows = ctypes.c_int32()
-    assert host.L.ifdlbm_autotune(h, 3, ctypes.byref(rows), None) == 0
+    """Small cavities, on a stand-in whose tiles are faster than any march and whose fastest march has 40 rows to an item:
+    the tuned handle steps on tiles, as the untuned one does, in one launch or one per cavity; the rows it reports are a
+    length of the march, the fastest one, for another handle."""
+    sizes = [(33, 240), (65, 240)]   # 6 segments at 40 rows, 5 at 48
+    h = host.create(sizes, precision=precision, batched=batched)
+    rows, ms = ctypes.c_int32(), ctypes.c_double()
+    host.L.host_cheap_rows(40)
+    assert host.L.ifdlbm_autotune(h, 3, ctypes.byref(rows), ctypes.byref(ms)) == 0
     assert host.L.ifdlbm_step(h, 1) == 0 and host.last_kernel() == "tile"
     assert host.faults() == (0, "")
+    host.L.ifdlbm_destroy(h)
+    assert rows.value == 40 and ms.value == (1.0 if batched else 2.0)
+    h = host.create(sizes, precision=precision, batched=batched, segment_rows=rows.value)
+    assert host.L.ifdlbm_step(h, 1) == 0 and host.last_kernel() == ("block" if precision in ("fp64", "fp32x", "fp32sr") else "march")
     host.L.ifdlbm_destroy(h)
