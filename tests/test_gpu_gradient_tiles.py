@@ -2,6 +2,7 @@
 (8 and 12 nodes), against the complex-step derivative of the CPU oracle: both
 are the derivative of the same discrete map to rounding (1e-9 relative per
 parameter, 1e-12 on J, the bars of the other comparisons with it)."""
+import numpy as np
 import pytest
 
 import oracle as O
@@ -28,3 +29,42 @@ def test_gradients_at_tile_edges(grid):
         assert abs(J - J_ref) <= 1e-12 * J_ref, name
         for q in range(3):
             assert abs(g[q] - g_ref[q]) <= 1e-9 * abs(g_ref[q]), (name, q)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp32x", "fp32sr", "fp32srf", "fp16dev"])
+def test_adjoint_clear_of_the_walls_in_the_storage_modes(precision):
+    """The reverse kernel's copy for tiles clear of the walls (past 256 tiles of 12 x 12) reads the stored states: two
+    checkpoint segments of the FP64 step linearised about the trajectory of the storage mode, against the oracle's step by
+    the complex step from each of that trajectory's states (the bars of the FP64 comparison).  One call per step draws
+    the random words that the adjoint draws."""
+    import ctypes
+    import math
+
+    from oracle import complex_step as CS
+    nx, ny, steps, hs = 205, 194, 6, 1e-20
+    re, n, th, u = 120.0, 0.8, 55.0, 0.1
+    cav, o = M.Cavity(nx, ny, re, n, th, u), M.ifdlbm_default_options(precision=precision, rho0=0.0)
+    h = M.ifdlbm_create([cav], o)
+    states = [M.ifdlbm_get_state(h, 0)]
+    for _ in range(steps):
+        M.ifdlbm_step(h, 1)
+        states.append(M.ifdlbm_get_state(h, 0))
+    h.close()
+    L, p, g_ref = CS.lib(), O.Params(nx=nx, ny=ny, re=re, n=n, theta_deg=th, u_lid=u, rho0=0.0), []
+    for dx in ({"theta_deg": hs * 180.0 / math.pi}, {"n": hs}, {"u_lid": hs}):
+        c = CS._cparams(p, dx)
+        F, lam = np.zeros((9, ny, nx), dtype=np.complex128), np.zeros((ny, nx), dtype=np.complex128)
+        assert L.orc_init(ctypes.byref(c), F.ctypes.data, lam.ctypes.data) == 0
+        for t, (f, l) in enumerate(states):
+            F.real, lam.real = f, l
+            if t < steps:
+                assert L.orc_run(ctypes.byref(c), F.ctypes.data, lam.ctypes.data, 1, None, None) == 0
+        J = CS._C()
+        L.orc_kinetic_energy_into(ctypes.byref(c), F.ctypes.data, ctypes.byref(J))
+        J_ref = J[0]
+        g_ref.append(J[1] / hs)
+    J, g = M.ifdlbm_adjoint(cav, o, steps, 3)
+    print(precision, J, J_ref, g, g_ref, flush=True)
+    assert abs(J - J_ref) <= 1e-12 * J_ref
+    for q in range(3):
+        assert abs(g[q] - g_ref[q]) <= 1e-9 * abs(g_ref[q]), q

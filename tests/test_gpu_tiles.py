@@ -52,3 +52,20 @@ def test_tile_shapes_equal_march_bitwise(precision, batched):
         print(precision, batched, nx, ny, count, flush=True)
         compare([M.Cavity(nx, ny, 100.0 + 300.0 * c, 0.6 + 0.1 * c, 90.0 - 5.0 * c) for c in range(count)], precision, 6,
                 batched=batched)
+
+
+# remainders on both axes; tiles of 24 x 8 and of 24 x 24 (shapes 1 and 2): the columns and rows of a tile, and the batch
+LARGER = [((131, 99), 4, (24, 8)), ((259, 251), 2, (24, 24))]
+
+
+@pytest.mark.parametrize("batched", [1, 0])
+@pytest.mark.parametrize("implicit", [0, 1])
+@pytest.mark.parametrize("precision", PRECISIONS)
+def test_larger_tiles_equal_march_in_every_mode(precision, implicit, batched):
+    for (nx, ny), count, (cols, rows) in LARGER:
+        print(precision, implicit, batched, nx, ny, flush=True)
+        cavs = [M.Cavity(nx, ny, 100.0 + 300.0 * c, 0.6 + 0.1 * c, 90.0 - 5.0 * c) for c in range(count)]
+        h = M.ifdlbm_create(cavs, M.ifdlbm_default_options(precision=precision))
+        assert M.ifdlbm_info(h)["work_items"] == count * -(-nx // cols) * -(-ny // rows)
+        h.close()
+        compare(cavs, precision, 6, lambda_mode=implicit, batched=batched)
