@@ -247,7 +247,8 @@ __global__ __launch_bounds__(threads_of(T), T == 8 ? 1 : 2) void t_step(TParams 
     constexpr int kSide = side_of(T), kNodes = kSide * kSide;
     __shared__ TangentLds<T> sh;
     const int nx = c.nx, ny = c.ny, t = min((int)threadIdx.x, kNodes - 1), lx = t % kSide, ly = t / kSide;
-    const int i0 = (int)blockIdx.x * T, j0 = (int)blockIdx.y * T, i = i0 - kHalo + lx, j = j0 - kHalo + ly;
+    const int tx = (nx + T - 1) / T, by = (int)blockIdx.x / tx, bx = (int)blockIdx.x - by * tx;
+    const int i0 = bx * T, j0 = by * T, i = i0 - kHalo + lx, j = j0 - kHalo + ly;
     const int64_t pl = (int64_t)nx * ny;
     // the nearest node of the grid: threads outside it compute a node that nothing reads
     const int64_t id = (int64_t)min(max(j, 0), ny - 1) * nx + min(max(i, 0), nx - 1);
@@ -473,7 +474,8 @@ hipError_t tangent_run(const TParams& P, const std::vector<D3>& geo, D3* work, i
     const int tile = ((P.nx + 7) / 8) * ((P.ny + 7) / 8) <= 256 ? 8 : 12;
     const auto step = tile == 8 ? t_step<8> : t_step<12>;
     const int threads = tile == 8 ? threads_of(8) : threads_of(12);
-    const dim3 tiles((P.nx + tile - 1) / tile, (P.ny + tile - 1) / tile);
+    // one dimension: tall grids have more rows of tiles than the 65536 workgroups of a launch's second dimension
+    const dim3 tiles((unsigned)((P.nx + tile - 1) / tile) * (unsigned)((P.ny + tile - 1) / tile));
     hipLaunchKernelGGL(t_init, g, blk, 0, s, P, b.f[0], b.l[0]);
     if ((e = hipGetLastError()) != hipSuccess) return failed(e, "Step (1) launch");
     int cur = 0;

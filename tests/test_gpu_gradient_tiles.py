@@ -68,3 +68,14 @@ def test_adjoint_clear_of_the_walls_in_the_storage_modes(precision):
     assert abs(J - J_ref) <= 1e-12 * J_ref
     for q in range(3):
         assert abs(g[q] - g_ref[q]) <= 1e-9 * abs(g_ref[q]), q
+
+
+def test_tangent_of_a_very_tall_grid():
+    """More rows of tiles (of 12 nodes) than the second dimension of a launch holds (65536 workgroups): two steps of the
+    tangent sweep against the adjoint, derivatives of one discrete map (the bars of the other comparison of the two)."""
+    cav, o = M.Cavity(5, 12 * 65536 + 17, 100.0, 0.8, 60.0), M.ifdlbm_default_options()
+    (Jt, gt), (Ja, ga) = M.ifdlbm_gradient(cav, o, 2), M.ifdlbm_adjoint(cav, o, 2, 2)
+    print(Jt, gt, Ja, ga, flush=True)
+    assert abs(Ja - Jt) <= 1e-11 * abs(Jt)
+    for q in range(3):
+        assert abs(ga[q] - gt[q]) <= 1e-9 * abs(gt[q]) + 1e-13 * np.abs(gt).max(), q
