@@ -337,7 +337,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_adjoint_step(AdjParams p, TileF
         const double gamma2 = 18.0 * Q * r * r;
         floor = !(gamma2 > p.g2min);
         m = floor ? p.g2min : gamma2;
-        pw = pow_pos<double>(m, p.expo);
+        pw = pow_pos<double>(m, p.expo);   // the power of the FP64 step: lambda as the trajectory took it
         lam = p.K3 * pw;
         const double bb = 1.5 * p.dt / (2.0 * lam + p.dt);
 #pragma unroll

@@ -140,7 +140,10 @@ __device__ __forceinline__ D3 relax_coef(double scale, const Th& dt, double m, c
 }
 
 // Steps (2)-(4): lambda (Eqs. 2.12-2.14, 1.4, every parameter differentiated: no Newtonian shortcut, as d mu / d n != 0
-// at n = 1), f-bar+ (Eq. 2.16) and f-hat+ (Eq. 2.15, over g) of a node.
+// at n = 1), f-bar+ (Eq. 2.16) and f-hat+ (Eq. 2.15, over g) of a node.  The power is the library's, within an ulp: that
+// of the step kernels (about two) saves 2 % of a sweep of 129 x 129 nodes, but takes the root-mean-square error of
+// (J, dJ/d theta, dJ/dn, dJ/dU) over 14 cavities, against extended precision, from (1.07, 0.39, 34, 1.13) to (1.10, 0.43,
+// 36, 1.14) e-15.
 __device__ __forceinline__ void collide_t(D3 (&g)[9], const D3& lam_old, const TParams& c, D3 (&bp)[9], D3& lam)
 {
     D3 P, ux, uy, n[9];
@@ -153,7 +156,7 @@ __device__ __forceinline__ void collide_t(D3 (&g)[9], const D3& lam_old, const T
     const double r = 1.0 / (2.0 * lam_old.v + c.dt.v);
     const double Q = pxx.v * pxx.v + 2.0 * pxy.v * pxy.v + pyy.v * pyy.v, g2 = 18.0 * Q * r * r;
     const bool floored = !(g2 > c.g2min);
-    const double m = floored ? c.g2min : g2, pw = pow_pos<double>(m, c.expo.v), lm = log(m);
+    const double m = floored ? c.g2min : g2, pw = pow(m, c.expo.v), lm = log(m);
     lam.v = 3.0 * c.K.v * pw;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
