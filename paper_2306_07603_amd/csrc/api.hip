@@ -118,7 +118,8 @@ struct ifdlbm_s {
     int32_t *d_unit_first = nullptr, *d_unit_count = nullptr;
     double* d_partial = nullptr;
     double* d_res = nullptr;                        // n_cav * kResult
-    double* h_res = nullptr;                        // pinned copy of d_res, made by the first read
+    double* h_res = nullptr;                        // pinned copy of d_res, made by the first read,
+    std::vector<double> page_res;                   // or a pageable one where no memory can be pinned
     double* d_ref = nullptr;                        // n_cav * 2 shifts of the residual sums
     double* d_scratch = nullptr;                    // 10 * max nodes doubles
     uint32_t* d_seed = nullptr;                     // stochastic-rounding step counter
@@ -588,17 +589,17 @@ int check_cav(const ifdlbm_s* h, int32_t c)
 // which made a check of run_to_steady every 10 steps of a 65 x 65 cavity 101 instead of 80 us.
 int read_residuals(ifdlbm_s* h, const double** sums)
 {
-    const size_t bytes = (size_t)h->n_cav * kResult * sizeof(double);
-    if (!h->h_res) {
-        hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&h->h_res), bytes, hipHostMallocDefault);
-        if (e != hipSuccess) {
-            h->h_res = nullptr;
-            return fail(IFDLBM_ENOMEM, std::string("hipHostMalloc: ") + hipGetErrorString(e));
-        }
+    const size_t n = (size_t)h->n_cav * kResult;
+    if (!h->h_res && h->page_res.empty() &&
+        hipHostMalloc(reinterpret_cast<void**>(&h->h_res), n * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();   // not for the next launch to report
+        h->h_res = nullptr;
+        h->page_res.resize(n);
     }
-    IFD_HIP(hipMemcpyAsync(h->h_res, h->d_res, bytes, hipMemcpyDeviceToHost, h->stream));
+    double* to = h->h_res ? h->h_res : h->page_res.data();
+    IFD_HIP(hipMemcpyAsync(to, h->d_res, n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     IFD_HIP(hipStreamSynchronize(h->stream));
-    *sums = h->h_res;
+    *sums = to;
     return IFDLBM_OK;
 }
 

@@ -19,6 +19,7 @@ namespace {
 std::map<const char*, size_t> live;       // device allocations
 size_t live_bytes = 0, peak_bytes = 0;
 long allocations_left = -1, pinned_left = -1;   // until an allocation fails (-1: never)
+hipError_t last_error = hipSuccess;       // as a launch reports it
 int faults = 0;
 std::string first_fault, last_kernel;
 std::vector<int> converged;               // per cavity: what the next residual reduction reports
@@ -56,13 +57,13 @@ void submit(std::function<void()> f)
 
 hipError_t take(void** p, size_t bytes, long& left)
 {
-    if (left == 0) return hipErrorOutOfMemory;
+    if (left == 0) return last_error = hipErrorOutOfMemory;
     if (left > 0) --left;
     *p = std::malloc(bytes);
     return *p ? hipSuccess : hipErrorOutOfMemory;
 }
 
-void step(const char* kernel, int prec, const ifd::StepArgs& a, const ifd::StripItem* items, int w0, int nw, bool residual)
+hipError_t step(const char* kernel, int prec, const ifd::StepArgs& a, const ifd::StripItem* items, int w0, int nw, bool residual)
 {
     const std::string name = kernel;
     submit([=] {
@@ -85,6 +86,7 @@ void step(const char* kernel, int prec, const ifd::StepArgs& a, const ifd::Strip
         }
         clock_ms += name == "tile" ? 1.0 : 10.0 + 0.1 * std::abs(rows - cheap_rows);
     });
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -97,6 +99,7 @@ void host_reset(long fail_after, long pinned_after)
     pinned_left = pinned_after;
     faults = 0;
     first_fault.clear();
+    last_error = hipSuccess;
     peak_bytes = live_bytes;
 }
 void host_converge(const int* flags, int n) { converged.assign(flags, flags + n); }
@@ -218,6 +221,12 @@ hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b)
     *ms = (float)(*reinterpret_cast<double*>(b) - *reinterpret_cast<double*>(a));
     return hipSuccess;
 }
+hipError_t hipGetLastError()
+{
+    const hipError_t e = last_error;
+    last_error = hipSuccess;
+    return e;
+}
 const char* hipGetErrorString(hipError_t e) { return e == hipErrorOutOfMemory ? "out of memory" : "error"; }
 
 }  // extern "C"
@@ -241,19 +250,16 @@ hipError_t launch_staged_step(int, const StepArgs& a, const NodeBlock* blocks, i
 }
 hipError_t launch_fused_step(int prec, bool, const StepArgs& a, const StripItem* items, int w0, int nw, bool residual, hipStream_t)
 {
-    step("march", prec, a, items, w0, nw, residual);
-    return hipSuccess;
+    return step("march", prec, a, items, w0, nw, residual);
 }
 hipError_t launch_block_step(int prec, bool, const StepArgs& a, const StripItem* items, int w0, int nw, bool residual, hipStream_t)
 {
-    step("block", prec, a, items, w0, nw, residual);
-    return hipSuccess;
+    return step("block", prec, a, items, w0, nw, residual);
 }
 hipError_t launch_tile_step(int, int prec, bool, const StepArgs& a, const StripItem* items, int w0, int nw, bool residual,
                             hipStream_t)
 {
-    step("tile", prec, a, items, w0, nw, residual);
-    return hipSuccess;
+    return step("tile", prec, a, items, w0, nw, residual);
 }
 hipError_t launch_reduce_partials(const double* partial, const int32_t* first, const int32_t* count, const CavityDesc* desc,
                                   int n_cav, double*, double* out, hipStream_t)

@@ -153,3 +153,18 @@ def test_autotune_keeps_a_faster_automatic_choice(host, precision, batched):
     h = host.create(sizes, precision=precision, batched=batched, segment_rows=rows.value)
     assert host.L.ifdlbm_step(h, 1) == 0 and host.last_kernel() == ("block" if precision in ("fp64", "fp32x", "fp32sr") else "march")
     host.L.ifdlbm_destroy(h)
+
+
+def test_residuals_without_pinned_memory(host):
+    """Where no host memory can be pinned, residuals are read into pageable memory, and the steps after go on."""
+    h = host.create([(33, 33)] * 3)
+    host.L.host_reset(-1, 0)
+    host.converge([0, 1, 0])
+    assert host.L.ifdlbm_step(h, 1) == 0
+    res = np.zeros(3)
+    for _ in range(2):
+        assert host.L.ifdlbm_get_residuals(h, res.ctypes.data, None) == 0
+        assert list(res) == [1.0, 0.0, 1.0]
+        assert host.L.ifdlbm_step(h, 1) == 0
+    assert host.faults() == (0, "")
+    host.L.ifdlbm_destroy(h)
