@@ -269,8 +269,9 @@ int ifdlbm_gradient_noalloc(const ifdlbm_cavity* cav, const ifdlbm_options* opt,
    reverse sweep recomputes each segment from its checkpoint and walks it backwards through the transposed
    Steps (2)-(6) of Section 4 in FP64, accumulating the parameter adjoints in FP64.  With an FP32 storage mode
    the gradient is that of the FP64 step linearised about the FP32 trajectory.  Device memory: the stored state
-   once per checkpoint and once per step of a segment (min(checkpoint_every, n_steps) + 1), and about 20 doubles
-   per node of work arrays, in one allocation made and freed inside the call, which synchronises the stream.
+   once per checkpoint and once per step of a segment (min(checkpoint_every, n_steps) + 1), its rows padded to the
+   pitch of ifdlbm_create only in the modes with stochastic rounding, and about 20 doubles per node of work arrays, in
+   one allocation made and freed inside the call, which synchronises the stream.
    Errors: EINVAL, ENOMEM, EDEVICE, EDIVERGED (non-finite trajectory or adjoint). */
 int ifdlbm_adjoint(const ifdlbm_cavity* cav, const ifdlbm_options* opt, int64_t n_steps, int32_t checkpoint_every,
                    int32_t objective, double* J, double grad[3]);

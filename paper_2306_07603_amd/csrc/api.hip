@@ -686,7 +686,9 @@ int ifdlbm_default_options(ifdlbm_options* opt)
     return IFDLBM_OK;
 }
 
-static int ifdlbm_create_impl(const ifdlbm_cavity* cav, int32_t n_cav, const ifdlbm_options* opt, ifdlbm_t** out)
+// pitch_of: rows of a plane start at multiples of that many elements
+static int ifdlbm_create_impl(const ifdlbm_cavity* cav, int32_t n_cav, const ifdlbm_options* opt, ifdlbm_t** out,
+                              int32_t pitch_of = 16)
 {
     if (!out) return fail(IFDLBM_EINVAL, "null output handle pointer");
     *out = nullptr;
@@ -757,7 +759,7 @@ static int ifdlbm_create_impl(const ifdlbm_cavity* cav, int32_t n_cav, const ifd
         std::memset(&d, 0, sizeof(d));
         d.nx = v.n_xi;
         d.ny = v.n_eta;
-        d.pitch = (v.n_xi + 15) / 16 * 16;
+        d.pitch = (v.n_xi + pitch_of - 1) / pitch_of * pitch_of;
         d.active = 1;
         d.plane = (int64_t)d.ny * d.pitch;
         d.f_off = f_off;
@@ -1232,8 +1234,13 @@ static int ifdlbm_adjoint_impl(const ifdlbm_cavity* cav, const ifdlbm_options* o
     o.graph_steps = 0;                 // one eager call per step: recomputation draws the same random words
     o.residual_every = 1 << 30;        // no residual work inside the sweeps
     o.batched = 1;
+    // The trajectory is kept as the step kernels store it.  Its rows are packed: padded to 16 they took up to 1.9 times
+    // the memory on grids from 17 columns, more than the FP64 states without padding that the sweep kept before.  The
+    // random words of a node follow its padded index, so the modes that draw them keep the padding; their states are
+    // half as large, or less.
+    const bool words = o.precision == IFDLBM_FP32SR || o.precision == IFDLBM_FP32SRF || o.precision == IFDLBM_FP16DEV;
     ifdlbm_t* h = nullptr;
-    int rc = ifdlbm_create(cav, 1, &o, &h);
+    int rc = ifdlbm_create_impl(cav, 1, &o, &h, words ? 16 : 1);
     if (rc) return rc;
     const CavityDesc c = h->desc[0];
     const int prec = h->opt.precision;

@@ -30,6 +30,9 @@ class Host:
         L.ifdlbm_set_state.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p]
         L.ifdlbm_autotune.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32),
                                       ctypes.POINTER(ctypes.c_double)]
+        L.ifdlbm_adjoint.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32,
+                                     ctypes.c_void_p, ctypes.c_void_p]
+        L.host_peak_bytes.restype = L.host_live_bytes.restype = ctypes.c_long
         L.ifdlbm_destroy.argtypes = [ctypes.c_void_p]
         L.ifdlbm_destroy.restype = None
         L.host_reset.argtypes = [ctypes.c_long, ctypes.c_long]
@@ -168,3 +171,23 @@ def test_residuals_without_pinned_memory(host):
         assert host.L.ifdlbm_step(h, 1) == 0
     assert host.faults() == (0, "")
     host.L.ifdlbm_destroy(h)
+
+
+@pytest.mark.parametrize("precision", PRECISIONS)
+@pytest.mark.parametrize("size", [(17, 400), (129, 129), (16, 64)])
+def test_adjoint_memory(host, size, precision):
+    """A trajectory takes no more device memory than one FP64 value per population and node and step, whatever the pitch:
+    the states of a segment and the checkpoints (100 steps in segments of 50), and at most 60 doubles per node of work
+    arrays and two padded states of the handle beside its scratch and lists."""
+    nx, ny = size
+    nodes, padded = nx * ny, -(-nx // 16) * 16 * ny
+    J, grad = np.zeros(1), np.zeros(3)
+    cav, o = M.Cavity(nx, ny, 400.0, 0.8, 60.0).c(), M.ifdlbm_default_options(precision=precision)
+    host.L.host_reset(-1, -1)
+    before = host.L.host_live_bytes()
+    assert host.L.ifdlbm_adjoint(ctypes.byref(cav), ctypes.byref(o), 100, 50, 0, J.ctypes.data, grad.ctypes.data) == 0
+    peak = host.L.host_peak_bytes() - before
+    limit = 80 * nodes * (50 + 1) + 2 * 80 * padded + 60 * 8 * nodes + 2 * 80 * padded + 80 * nodes + 300 * nodes // 8 + 100000
+    print(size, precision, peak, limit)
+    assert peak <= limit
+    assert host.L.host_live_bytes() == before and host.faults() == (0, "")
