@@ -253,10 +253,10 @@ int ifdlbm_gradient(const ifdlbm_cavity* cav, const ifdlbm_options* opt, int64_t
 
 /* ifdlbm_gradient for callers that cannot allocate device memory (code under HIP graph capture is not among
    them: the call synchronises), such as tight serving loops and harnesses that forbid hipMalloc: the same
-   J and grad[3], bitwise, with no hipMalloc, hipFree or stream creation.  The work arrays (48 values of 32
-   bytes per node, plus n_xi + n_eta + nodes / 256) live in a 32 MiB array of the library's device code, one
-   per GPU, held until the process ends; grids needing more (beyond about 21 800 nodes: 147 x 147 fits) are
-   rejected with EINVAL before any device work.  The current device's array is used; options.hip_stream NULL
+   J and grad[3], bitwise, with no hipMalloc, hipFree or stream creation.  The work arrays (20 values of 32
+   bytes per node) live in a 32 MiB array of the library's device code, one per GPU, held until the process ends;
+   grids for which 48 values per node, n_xi + n_eta and nodes / 256 exceed it (beyond about 21 800 nodes: 147 x
+   147 fits) are rejected with EINVAL before any device work.  The current device's array is used; options.hip_stream NULL
    means the null stream.  Every call on a GPU shares that GPU's array: calls that overlap on one GPU (from two
    threads, or on two streams without ordering) race and give wrong results.  Nothing of a previous call's
    contents is read (every value is written before it is read).  Errors: EINVAL, EDEVICE. */

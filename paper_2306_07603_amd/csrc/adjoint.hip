@@ -219,10 +219,11 @@ __global__ __launch_bounds__(kB) void a_objective(AdjParams p, double cot, const
 // BH, C^T, BH^T and the wall transpose (one more for the wall nodes next to
 // those), 0 for B^T and A^T.  Parameter adjoints are summed over the nodes of
 // the tile proper.
-// Bound by the chain of FP64 instructions of a thread (2330, with wall handling
-// 3560, at 8 to 10 cycles each with two wavefronts per SIMD): 17 us on 33 x 33
-// and 20 us on 129 x 129 nodes, where the nine launches of a stage each, through
-// HBM, took 105 us.  Tiles of 8 x 8 recompute more halo (50 against 45 us per
+// Bound by the chain of a thread: 2230 vector and 245 LDS instructions of a
+// wavefront on 129 x 129 nodes (1660 and 227 clear of the walls), 55 % of its
+// time spent waiting (dependent FP64 instructions, LDS, five barriers, 16 to 36
+// spilled registers): 20 us on 33 x 33 and 21 us on 129 x 129 nodes, where the
+// nine launches of a stage each, through HBM, took 105 us.  Tiles of 8 x 8 recompute more halo (50 against 45 us per
 // step of the whole adjoint on 129 x 129 before the walls' loops left their
 // arrays), tiles of 16 x 16 leave 168 registers per thread, which spill (59 us).
 constexpr int kTile = 12, kHalo = 4, kSide = kTile + 2 * kHalo;

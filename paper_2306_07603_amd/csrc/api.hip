@@ -233,7 +233,12 @@ BlockPlan plan_block(const ifdlbm_s* h, int one_cav)
 // per CU only: a second round of it loses to shape 1 until there are about six; a round of shape 1 (two workgroups per
 // CU) takes 6.3 .. 7.7 us beyond some five rounds, a round of shape 2 10.0 .. 11.0 us, a chunk and round of the march
 // 4.5 .. 5.3 us at these sizes.  Which of them is least follows the grids, not the node count alone (a strip of a 65
-// wide cavity uses 33 of its 64 lanes), so the three are compared.
+// wide cavity uses 33 of its 64 lanes), so the three are compared.  These figures are for FP64 and FP32SRF with the lagged
+// lambda, all cavities in one launch, without residual sums.  The same lines decide for the other modes of the same
+// arithmetic, the implicit lambda, residual steps and launches per cavity, where they were not drawn anew: over 420
+// configurations of these on 20 batches, 33^2 to 40 x 513^2, nothing is slower than the row march that all of them took
+// before (1.005 to 7.8 times as fast), but another choice may be faster still (a residual step of the FP64 march takes
+// 1.3 times a plain one).
 constexpr int kMarch = -1;
 constexpr int64_t kShape1Tiles2 = 6 * kCus;   // FP64: tiles of shape 2 up to which shape 1 is considered
 

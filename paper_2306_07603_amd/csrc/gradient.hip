@@ -176,11 +176,12 @@ __device__ __forceinline__ void collide_t(D3 (&g)[9], const D3& lam_old, const T
 // One step of a tile of T x T nodes with every derivative, as step_tile.hip
 // does it: the workgroup holds the tile and four more nodes on every side, one
 // per thread; f-bar+ and then f(t + dt/2) in LDS (a plane per population and
-// component), f-hat+ in registers.  Bound by the chain of about 3500 FP64
-// instructions of a thread.  Five launches of a stage each through HBM took 44
-// us per step on 33 x 33 and 47 us on 129 x 129 nodes; tiles of 8 take 18 and 29
-// us (342 registers, one wavefront per SIMD), tiles of 12, with less halo and
-// two wavefronts per SIMD, 25 and 27 us (256 registers, some spilled).
+// component), f-hat+ in registers.  Bound by the chain of about 2500 vector
+// instructions of a wavefront, mostly FP64, with 40 % (33 x 33) to 54 % (129 x
+// 129) of its time spent waiting.  Five launches of a stage each through HBM
+// took 44 us per step on 33 x 33 and 47 us on 129 x 129 nodes; tiles of 8 take 17
+// and 29 us (342 registers, one wavefront per SIMD), tiles of 12, with less halo
+// and two wavefronts per SIMD, 25 and 27 us (256 registers, 78 more spilled).
 constexpr int kHalo = 4;
 constexpr int side_of(int T) { return T + 2 * kHalo; }
 constexpr int threads_of(int T) { return (side_of(T) * side_of(T) + kWaveLanes - 1) / kWaveLanes * kWaveLanes; }
@@ -459,7 +460,7 @@ TBuf carve(D3* w, size_t nn, size_t ngeo)
     return b;
 }
 
-// The sweep in a given workspace: Step (1), n_steps staged steps with their derivatives, Eq. (5.1).  Every
+// The sweep in a given workspace: Step (1), n_steps steps with their derivatives, Eq. (5.1).  Every
 // work array is written before it is read, so the workspace needs no clearing.
 hipError_t tangent_run(const TParams& P, const std::vector<D3>& geo, D3* work, int64_t n_steps, hipStream_t s,
                        double* J, double* grad, std::string& err)

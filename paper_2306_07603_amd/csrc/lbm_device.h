@@ -231,8 +231,8 @@ template <> struct Storage<P_FP16DEV> {
 __host__ __device__ constexpr int cxk(int k) { return k == 1 || k == 5 || k == 8 ? 1 : (k == 3 || k == 6 || k == 7 ? -1 : 0); }
 __host__ __device__ constexpr int cyk(int k) { return k == 2 || k == 5 || k == 6 ? 1 : (k == 4 || k == 7 || k == 8 ? -1 : 0); }
 
-// a b + c in one rounding (a general a * b + c for the derivative types).
-template <typename T> __device__ __forceinline__ T fused(T a, T b, T c) { return a * b + c; }
+// a b + c in one rounding.
+template <typename T> __device__ __forceinline__ T fused(T a, T b, T c);
 template <> __device__ __forceinline__ float fused<float>(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 template <> __device__ __forceinline__ double fused<double>(double a, double b, double c) { return __builtin_fma(a, b, c); }
 

@@ -19,9 +19,14 @@
 // Microseconds per FP64 step, that march against this one (each at its segment
 // length): 64 x 513^2 946 / 925, 200 x 257^2 794 / 776, 16 x 513^2 290 / 260,
 // one 1025^2 93 / 62; against the tiles where those were chosen before,
-// 13 x 257^2 64 / 56, 4 x 513^2 70 / 62.  Bound by the issue of FP64
-// instructions (about 700 per row and lane at 5.2 cycles: 64 % of the time of
-// 64 x 513^2) and the waits at the two barriers of a chunk.
+// 13 x 257^2 64 / 56, 4 x 513^2 70 / 62.  Not bound by one thing (counters, 64
+// x 513^2 and the 256-cavity batch alike): vector instructions, 580 per row and
+// wavefront, are issued at 35 .. 37 % of the peak rate (FP64 ones, at the 5.2
+// cycles they were measured to take, for 45 .. 49 % of the time), and the two
+// wavefronts of a SIMD spend 51 % of their time waiting, 3 % of it for LDS
+// issue: for the loads of a chunk and at its two barriers.  The residual
+// variants hold nine more values from chunk to chunk and spill 73 to 87
+// registers (13 x 257^2 with residual sums 72.5 us, without 56.0).
 #include "ifdlbm_internal.h"
 #include "step_common.h"
 

@@ -216,7 +216,7 @@ __device__ __forceinline__ void wall_source(T (*w)[9], int i, int nx, const T (&
 
 // One work item.  Register ring slot of row t - d at unrolled phase R:
 // (R + 5 - d) % 5 for f-bar+ and lambda (d = 0..4), (R + 10 - d) % 5 for
-// f(t + dt/2) (d = 2..6); with one row per trip R is 0 and the rings move.
+// f(t + dt/2) (d = 2..6).
 template <int PREC, bool RES, bool IMPL>
 struct March {
     using S = Storage<PREC>;
@@ -315,8 +315,7 @@ struct March {
         march(t_begin, t_end);
     }
 
-    // LDS ring slot of row r (a run-time index: the LDS ring is not moved when
-    // the register rings are)
+    // LDS ring slot of row r (a run-time index)
     __device__ __forceinline__ int hslot(int r) const { return (r - t_begin + 2 * kRing) % kRing; }
 
     __device__ __forceinline__ uint32_t foff(int row) const { return (uint32_t)(row * pitch + ic) * (uint32_t)sizeof(F); }

@@ -13,12 +13,12 @@
 //                          back into the same LDS tile
 //   C  (outputs)           f-hat(t + dt) by Eq. (3.6), walls by extrapolation
 //                          (Step 6), store, residual sums of Eq. (2.19)
-// What bounds it: for one small cavity the chain of one step, about 900
-// instructions of one wavefront behind two dependent loads (5.2 us per step
-// of a 33 x 33 FP32SRF cavity and 5.7 us in FP64, against 35.0 us of the FP32
-// march, whose items are chains of at least 16 rows); from about 256 x 256
-// nodes on the issue of vector instructions (78 % of the peak on 64 x 513^2 in
-// FP32SRF, shape 2).  The halo is recomputed: a 24 x 24 tile runs stage A on
+// What bounds it: for one small cavity the chain of one step, 340 vector
+// instructions of a wavefront in FP32SRF and 370 in FP64 behind two dependent
+// loads, with 70 % of its time spent waiting (5.2 us per step of a 33 x 33
+// FP32SRF cavity and 5.7 us in FP64, against 35.0 us of the FP32 march, whose
+// items are chains of at least 16 rows); on large batches the issue of vector
+// instructions (shape 2 in FP32SRF: 63 % of the peak on 1025^2, 79 % on 12 x 513^2).  The halo is recomputed: a 24 x 24 tile runs stage A on
 // 1.8 and stage B on 1.4 times its nodes, so past a few million nodes (in FP64
 // half a million) the march with its 1.3 wins (choose_kernel in api.hip holds the measured line).
 //
@@ -260,8 +260,8 @@ __device__ __forceinline__ void tile_item(const StepArgs& a, const StripItem& it
         }
 }
 
-// Tiles away from the walls take a copy of the code without wall handling (613 instead of about 850 vector
-// instructions per node in FP32SRF).  Four wavefronts per SIMD (128 registers) are asked for where tiles queue up on
+// Tiles away from the walls take a copy of the code without wall handling (vector instructions of a wavefront of 128
+// nodes in FP32SRF: 918 on 1025^2, where 9 % of the tiles are at a wall, 1048 on 513^2, where 17 % are).  Four wavefronts per SIMD (128 registers) are asked for where tiles queue up on
 // the CUs: in FP64 that and the fences of tile_transport took 64 x 513^2 from 1885 to 1305 us per step in shape 1.  The
 // small tile of shape 0 runs one round, where more registers are faster (5.7 against 6.4 us on 33 x 33).
 template <int PREC, bool RES, bool IMPL, int LX, int LY, int NPT>
