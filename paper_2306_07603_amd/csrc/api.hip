@@ -118,7 +118,7 @@ struct ifdlbm_s {
     int32_t *d_unit_first = nullptr, *d_unit_count = nullptr;
     double* d_partial = nullptr;
     double* d_res = nullptr;                        // n_cav * kResult
-    double* h_res = nullptr;                        // pinned copy of d_res,
+    double* h_res = nullptr;                        // pinned copy of d_res, made by the first read,
     std::vector<double> page_res;                   // or a pageable one where no memory can be pinned
     double* d_ref = nullptr;                        // n_cav * 2 shifts of the residual sums
     double* d_scratch = nullptr;                    // 10 * max nodes doubles
@@ -595,7 +595,12 @@ int check_cav(const ifdlbm_s* h, int32_t c)
 int read_residuals(ifdlbm_s* h, const double** sums)
 {
     const size_t n = (size_t)h->n_cav * kResult;
-    if (!h->h_res) h->page_res.resize(n);
+    if (!h->h_res && h->page_res.empty() &&
+        hipHostMalloc(reinterpret_cast<void**>(&h->h_res), n * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();   // not for the next launch to report
+        h->h_res = nullptr;
+        h->page_res.resize(n);
+    }
     double* to = h->h_res ? h->h_res : h->page_res.data();
     IFD_HIP(hipMemcpyAsync(to, h->d_res, n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     IFD_HIP(hipStreamSynchronize(h->stream));
@@ -852,21 +857,6 @@ static int ifdlbm_create_impl(const ifdlbm_cavity* cav, int32_t n_cav, const ifd
     rc = rebuild_worklists(h);
     if (rc) return bail(rc);
     *out = h;
-    return IFDLBM_OK;
-}
-
-// The handle of a caller, with the pinned buffer of its residual record: made here, as reading residuals is to allocate
-// nothing (another thread may be capturing a graph then, which an allocation would invalidate).
-static int create_with_record(const ifdlbm_cavity* cav, int32_t n_cav, const ifdlbm_options* opt, ifdlbm_t** out)
-{
-    const int rc = ifdlbm_create_impl(cav, n_cav, opt, out);
-    if (rc) return rc;
-    ifdlbm_t* h = *out;
-    if (hipHostMalloc(reinterpret_cast<void**>(&h->h_res), (size_t)n_cav * kResult * sizeof(double), hipHostMallocDefault) !=
-        hipSuccess) {
-        (void)hipGetLastError();   // not for the next launch to report
-        h->h_res = nullptr;
-    }
     return IFDLBM_OK;
 }
 
@@ -1473,7 +1463,7 @@ const char* ifdlbm_build_digest(void) { return IFD_SOURCE_DIGEST; }
 // C entry points: no C++ exception crosses the ABI.
 int ifdlbm_create(const ifdlbm_cavity* cav, int32_t n_cav, const ifdlbm_options* opt, ifdlbm_t** out)
 {
-    IFD_GUARD(create_with_record(cav, n_cav, opt, out));
+    IFD_GUARD(ifdlbm_create_impl(cav, n_cav, opt, out));
 }
 
 int ifdlbm_step(ifdlbm_t* h, int64_t n_steps)

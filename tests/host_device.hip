@@ -19,7 +19,6 @@ namespace {
 std::map<const char*, size_t> live;       // device allocations
 size_t live_bytes = 0, peak_bytes = 0;
 long allocations_left = -1, pinned_left = -1;   // until an allocation fails (-1: never)
-int pinned_calls = 0;
 hipError_t last_error = hipSuccess;       // as a launch reports it
 int faults = 0;
 std::string first_fault, last_kernel;
@@ -111,7 +110,6 @@ int host_faults(char* text, int size)
     return faults;
 }
 void host_last_kernel(char* text, int size) { std::snprintf(text, size, "%s", last_kernel.c_str()); }
-int host_pinned_calls() { return pinned_calls; }
 long host_peak_bytes() { return (long)peak_bytes; }
 long host_live_bytes() { return (long)live_bytes; }
 
@@ -138,11 +136,7 @@ hipError_t hipFree(void* p)
     std::free(p);
     return hipSuccess;
 }
-hipError_t hipHostMalloc(void** p, size_t bytes, unsigned)
-{
-    ++pinned_calls;
-    return take(p, bytes, pinned_left);
-}
+hipError_t hipHostMalloc(void** p, size_t bytes, unsigned) { return take(p, bytes, pinned_left); }
 hipError_t hipHostFree(void* p)
 {
     std::free(p);

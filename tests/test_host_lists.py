@@ -40,8 +40,8 @@ class Host:
         L.host_converge.argtypes = [ctypes.c_void_p, ctypes.c_int]
         L.host_converge.restype = None
 
-    def create(self, sizes, pinned=-1, **opt):
-        self.L.host_reset(-1, pinned)
+    def create(self, sizes, **opt):
+        self.L.host_reset(-1, -1)
         self.sizes = sizes
         arr = (M.ifdlbm.ifdlbm_cavity * len(sizes))(*[M.Cavity(a, b, 400.0, 0.8, 60.0).c() for a, b in sizes])
         o = M.ifdlbm_default_options(**opt)
@@ -160,7 +160,8 @@ def test_autotune_keeps_a_faster_automatic_choice(host, precision, batched):
 
 def test_residuals_without_pinned_memory(host):
     """Where no host memory can be pinned, residuals are read into pageable memory, and the steps after go on."""
-    h = host.create([(33, 33)] * 3, pinned=0)
+    h = host.create([(33, 33)] * 3)
+    host.L.host_reset(-1, 0)
     host.converge([0, 1, 0])
     assert host.L.ifdlbm_step(h, 1) == 0
     res = np.zeros(3)
@@ -169,18 +170,6 @@ def test_residuals_without_pinned_memory(host):
         assert list(res) == [1.0, 0.0, 1.0]
         assert host.L.ifdlbm_step(h, 1) == 0
     assert host.faults() == (0, "")
-    host.L.ifdlbm_destroy(h)
-
-
-def test_reading_residuals_allocates_nothing(host):
-    h = host.create([(33, 33)] * 2, residual_every=2)
-    host.exhaust()
-    pinned = host.L.host_pinned_calls()
-    host.converge([0, 0])
-    assert host.L.ifdlbm_step(h, 2) == 0
-    assert host.L.ifdlbm_get_residuals(h, None, None) == 0
-    assert host.L.ifdlbm_run_to_steady(h, TOL, 4, None, None, None) == M.IFDLBM_ENOTCONVERGED
-    assert host.L.host_pinned_calls() == pinned and host.faults() == (0, "")
     host.L.ifdlbm_destroy(h)
 
 
