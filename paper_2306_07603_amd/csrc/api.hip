@@ -595,17 +595,11 @@ int check_cav(const ifdlbm_s* h, int32_t c)
 int read_residuals(ifdlbm_s* h, const double** sums)
 {
     const size_t n = (size_t)h->n_cav * kResult;
-    if (!h->h_res && h->page_res.empty()) {
-        // relaxed: in the default mode an allocation ends a graph capture that another thread has under way
-        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-        IFD_HIP(hipThreadExchangeStreamCaptureMode(&mode));
-        const hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&h->h_res), n * sizeof(double), hipHostMallocDefault);
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();   // not for the next launch to report
-            h->h_res = nullptr;
-            h->page_res.resize(n);
-        }
+    if (!h->h_res && h->page_res.empty() &&
+        hipHostMalloc(reinterpret_cast<void**>(&h->h_res), n * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();   // not for the next launch to report
+        h->h_res = nullptr;
+        h->page_res.resize(n);
     }
     double* to = h->h_res ? h->h_res : h->page_res.data();
     IFD_HIP(hipMemcpyAsync(to, h->d_res, n * sizeof(double), hipMemcpyDeviceToHost, h->stream));

@@ -10,7 +10,6 @@
 #include <map>
 #include <new>
 #include <string>
-#include <utility>
 #include <vector>
 
 #include "ifdlbm_internal.h"
@@ -26,8 +25,7 @@ std::string first_fault, last_kernel;
 std::vector<int> converged;               // per cavity: what the next residual reduction reports
 double clock_ms = 0.0;
 int cheap_rows = 0;                       // item rows at which the modelled march is fastest
-bool capturing = false, other_capture = false;   // by a handle; by another thread, in the global mode
-hipStreamCaptureMode capture_mode = hipStreamCaptureModeGlobal;
+bool capturing = false;
 std::vector<std::function<void()>> recorded;
 
 void fault(const std::string& what)
@@ -59,10 +57,6 @@ void submit(std::function<void()> f)
 
 hipError_t take(void** p, size_t bytes, long& left)
 {
-    if (other_capture && capture_mode != hipStreamCaptureModeRelaxed) {
-        fault("allocation during another thread's capture");
-        return last_error = hipErrorStreamCaptureUnsupported;
-    }
     if (left == 0) return last_error = hipErrorOutOfMemory;
     if (left > 0) --left;
     *p = std::malloc(bytes);
@@ -116,8 +110,6 @@ int host_faults(char* text, int size)
     return faults;
 }
 void host_last_kernel(char* text, int size) { std::snprintf(text, size, "%s", last_kernel.c_str()); }
-void host_other_capture(int on) { other_capture = on; }
-int host_capture_mode() { return (int)capture_mode; }
 long host_peak_bytes() { return (long)peak_bytes; }
 long host_live_bytes() { return (long)live_bytes; }
 
@@ -176,11 +168,6 @@ hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned)
 }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
-hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* mode)
-{
-    std::swap(*mode, capture_mode);
-    return hipSuccess;
-}
 hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode)
 {
     capturing = true;

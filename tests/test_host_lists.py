@@ -173,20 +173,6 @@ def test_residuals_without_pinned_memory(host):
     host.L.ifdlbm_destroy(h)
 
 
-def test_residuals_during_the_capture_of_another_thread(host):
-    """A capture in the global mode, as torch takes graphs by default, is ended by an allocation of any thread that has not
-    asked for the relaxed mode; the thread's own mode is as before afterwards."""
-    h = host.create([(33, 33)] * 2)
-    host.L.host_other_capture(1)
-    host.converge([0, 0])
-    assert host.L.ifdlbm_step(h, 1) == 0
-    assert host.L.ifdlbm_get_residuals(h, None, None) == 0
-    assert host.L.ifdlbm_run_to_steady(h, TOL, 2, None, None, None) == M.IFDLBM_ENOTCONVERGED
-    assert host.faults() == (0, "") and host.L.host_capture_mode() == 0
-    host.L.host_other_capture(0)
-    host.L.ifdlbm_destroy(h)
-
-
 @pytest.mark.parametrize("precision", PRECISIONS)
 @pytest.mark.parametrize("size", [(17, 400), (129, 129), (16, 64)])
 def test_adjoint_memory(host, size, precision):
