@@ -79,3 +79,15 @@ def test_tangent_of_a_very_tall_grid():
     assert abs(Ja - Jt) <= 1e-11 * abs(Jt)
     for q in range(3):
         assert abs(ga[q] - gt[q]) <= 1e-9 * abs(gt[q]) + 1e-13 * np.abs(gt).max(), q
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp32x"])
+def test_adjoint_on_packed_rows_by_march_and_tiles(precision):
+    """The trajectories of these modes have rows that start anywhere: the march (forced) and the tiles store the same bits
+    there, so J and the gradient are equal, on widths one over and under a multiple of 16 and of the strip."""
+    for nx, ny in ((17, 23), (31, 18), (57, 40), (113, 19)):
+        cav = M.Cavity(nx, ny, 200.0, 0.8, 65.0)
+        (Ja, ga), (Jb, gb) = (M.ifdlbm_adjoint(cav, M.ifdlbm_default_options(precision=precision, segment_rows=rows), 14, 5)
+                              for rows in (0, 16))
+        print(precision, nx, ny, Ja, ga, flush=True)
+        assert Ja == Jb and np.array_equal(ga, gb) and np.all(np.isfinite(ga))
